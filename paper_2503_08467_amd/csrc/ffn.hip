@@ -128,7 +128,7 @@ __device__ __forceinline__ float epilogue(float u, float g) {
 template <int EPI>
 __device__ __forceinline__ float epilogue_fast(float u, float g) {
     if (EPI == kEpiGelu) return act_gelu_fast(u);
-    if (EPI == kEpiGeluTanh) return act_gelu_tanh(u);
+    if (EPI == kEpiGeluTanh) return act_gelu_tanh_fast(u);
     if (EPI == kEpiSwiglu) return silu_fast(u) * g;
     return u;
 }
@@ -372,23 +372,50 @@ struct LdsShape {
     static_assert(BK == 32, "the K-blocked operands come in blocks of 32");
 };
 
-// Stores one lane's share of a 32 x 32 bf16 output block.  The MFMA layout leaves lane
-// (row, half) with columns 8 q + 4 half .. 8 q + 4 half + 3 of its row, q = 0..3, packed
-// as pk[q].  Lanes l and l + 32 hold the same row; v_permlane32_swap trades lane l's pk[1]
-// for lane l + 32's pk[0] (and pk[3] for pk[2]), after which lane l holds columns 0..7 and
-// 16..23 of the row and lane l + 32 columns 8..15 and 24..31, each run stored as one
-// 16-byte vector: half the store instructions of 8-byte groups, and 32 contiguous bytes of
-// every row per instruction.  dst = the lane's row at column 8 half of the block (the
-// second run is dst + 16); ok0 / ok1 say whether each run is stored.  Every lane of the
-// wave must call it (the swap).
-__device__ __forceinline__ void store_block_bf16(bf16_t* dst, const uint2 (&pk)[4], bool ok0, bool ok1) {
-    // swap(vdst, src): lanes 32..63 of vdst <-> lanes 0..31 of src; returns {vdst, src}
+// Stores of a 32 x 32 output block.  The MFMA layout leaves lane (row l % 32, half l / 32)
+// with columns 8 q + 4 half .. 8 q + 4 half + 3 of its row, q = 0..3.  Stored like that, an
+// instruction writes 32 rows in pieces of 32 bytes; the lanes first trade their runs so that
+// every instruction writes 64 contiguous bytes of 16 rows: lane l stores rows l % 16 and
+// 16 + l % 16 of the block, the same columns of both.  Every lane of the wave must call (the
+// lane swaps).  Measured: 1024-column fp32 outputs 32.2 -> 31.2 us (8192 rows, K = 512),
+// 4096-column bf16 ones 109.4 -> 106.6 us (8192 rows, K = 1792).
+//
+// swap(vdst, src) of permlane32: lanes 32..63 of vdst <-> lanes 0..31 of src; of permlane16:
+// odd rows of 16 lanes of vdst <-> even rows of src; both return {vdst, src}.
+//
+// bf16: pk[q] holds the lane's four columns of run q.  After the permlane32 swaps lane l holds
+// columns 8 half .. + 7 and 16 + 8 half .. + 7 of its row, after the permlane16 swaps columns
+// c .. c + 7, c = store_col_bf16(), of the two rows.  d0 / d1: the rows' addresses there.
+__device__ __forceinline__ int store_col_bf16(int lane) { return 8 * (lane >> 5) + 16 * ((lane >> 4) & 1); }
+__device__ __forceinline__ void store_block_bf16(bf16_t* d0, bf16_t* d1, const uint2 (&pk)[4], bool ok0, bool ok1) {
     const auto a0 = __builtin_amdgcn_permlane32_swap(pk[0].x, pk[1].x, false, false);
     const auto a1 = __builtin_amdgcn_permlane32_swap(pk[0].y, pk[1].y, false, false);
     const auto b0 = __builtin_amdgcn_permlane32_swap(pk[2].x, pk[3].x, false, false);
     const auto b1 = __builtin_amdgcn_permlane32_swap(pk[2].y, pk[3].y, false, false);
-    if (ok0) *reinterpret_cast<uint4*>(dst) = make_uint4(a0[0], a1[0], a0[1], a1[1]);
-    if (ok1) *reinterpret_cast<uint4*>(dst + 16) = make_uint4(b0[0], b1[0], b0[1], b1[1]);
+    const auto x = __builtin_amdgcn_permlane16_swap(a0[0], b0[0], false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(a1[0], b1[0], false, false);
+    const auto z = __builtin_amdgcn_permlane16_swap(a0[1], b0[1], false, false);
+    const auto w = __builtin_amdgcn_permlane16_swap(a1[1], b1[1], false, false);
+    if (ok0) *reinterpret_cast<uint4*>(d0) = make_uint4(x[0], y[0], z[0], w[0]);
+    if (ok1) *reinterpret_cast<uint4*>(d1) = make_uint4(x[1], y[1], z[1], w[1]);
+}
+
+// fp32, runs q = 2 p and 2 p + 1 (u and v): after the swaps the lane holds columns
+// 16 p + store_col_f32() .. + 3 of the two rows.
+__device__ __forceinline__ int store_col_f32(int lane) { return 4 * (lane >> 5) + 8 * ((lane >> 4) & 1); }
+__device__ __forceinline__ void store_block_f32(float* d0, float* d1, const float (&u)[4], const float (&v)[4], bool ok0,
+                                                bool ok1) {
+    float4 r0, r1;
+    float* const o0 = &r0.x;
+    float* const o1 = &r1.x;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(u[c]), __float_as_uint(v[c]), false, false);
+        o0[c] = __uint_as_float(x[0]);
+        o1[c] = __uint_as_float(x[1]);
+    }
+    if (ok0) *reinterpret_cast<float4*>(d0) = r0;
+    if (ok1) *reinterpret_cast<float4*>(d1) = r1;
 }
 
 // One accumulator value for the epilogue.  With 256 accumulator registers per lane they
@@ -402,12 +429,6 @@ __device__ __forceinline__ float acc_read(float a) {
     asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
     return v;
 }
-
-// Row tile mt's expert and row range.
-struct TileRows {
-    int64_t row0, row_end;
-    int e;
-};
 
 // The row-tile table (first row tile of every expert): in LDS, written by tile_prefix ...
 struct LdsTiles {
@@ -464,28 +485,6 @@ struct RegTiles {
     }
 };
 
-template <int BM, typename Tiles>
-__device__ __forceinline__ TileRows tile_rows(const GroupedGemm& g, const Tiles& tiles, int mt) {
-    TileRows t;
-    t.e = __builtin_amdgcn_readfirstlane(tiles.find(mt));
-    const int first = __builtin_amdgcn_readfirstlane(tiles.start(t.e));
-    const int64_t seg0 = g.offsets[t.e], seg1 = g.offsets[t.e + 1];
-    t.row0 = seg0 + static_cast<int64_t>(mt - first) * BM;
-    t.row_end = seg1 < g.rows_max ? seg1 : g.rows_max;
-    return t;
-}
-
-// Logical tile L -> (row tile, column tile): groups of GM row tiles, column-major inside a
-// group, so that neighbouring tiles share either rows or weights.
-__device__ __forceinline__ void tile_coords(int L, int total_m, int n_tiles, int& mt, int& nt) {
-    constexpr int GM = 8;
-    const int grp = L / (GM * n_tiles);
-    const int rem = L - grp * GM * n_tiles;
-    const int gsz = min(GM, total_m - grp * GM);
-    nt = rem / gsz;
-    mt = grp * GM + (rem - nt * gsz);
-}
-
 // Where a tile's rows are read from.  The tile reads BM activation rows starting at
 // row_base and BN weight rows starting at n_base, both shifted back from the tile's own
 // first row / column when the tile would run past the end of the buffer (so every load
@@ -497,16 +496,24 @@ struct TileGeom {
 };
 
 template <int BM, int BN, typename Tiles>
-__device__ __forceinline__ TileGeom tile_geom(const GroupedGemm& g, const Tiles& tiles, int total_m, int L) {
-    int mt, nt;
-    tile_coords(L, total_m, g.n_tiles, mt, nt);
-    const TileRows tr = tile_rows<BM>(g, tiles, mt);
+__device__ __forceinline__ TileGeom tile_geom(const GroupedGemm& g, const Tiles& tiles, int L) {
     TileGeom t;
-    t.e = tr.e;
-    t.row0 = tr.row0;
-    t.row_end = tr.row_end;
+    t.e = __builtin_amdgcn_readfirstlane(tiles.find(L / g.n_tiles));
+    const int first = __builtin_amdgcn_readfirstlane(tiles.start(t.e));
+    const int64_t seg0 = g.offsets[t.e], seg1 = g.offsets[t.e + 1];
+    // tile L of the list is tile l of its expert's m x n_tiles tiles: groups of at most 8 row
+    // tiles, as even as they go, column-major inside a group
+    const int m = static_cast<int>((seg1 - seg0 + BM - 1) / BM);
+    const int l = L - first * g.n_tiles;
+    const int gsz = (m + (m + 7) / 8 - 1) / ((m + 7) / 8);
+    const int grp = l / (gsz * g.n_tiles);
+    const int rem = l - grp * gsz * g.n_tiles;
+    const int sz = min(gsz, m - grp * gsz);
+    const int nt = rem / sz, mt = grp * gsz + rem - nt * sz;
+    t.row0 = seg0 + static_cast<int64_t>(mt) * BM;
+    t.row_end = seg1 < g.rows_max ? seg1 : g.rows_max;
     const int64_t top = g.rows_max > BM ? g.rows_max - BM : 0;
-    t.row_base = tr.row0 < 0 ? 0 : (tr.row0 > top ? top : tr.row0);
+    t.row_base = t.row0 < 0 ? 0 : (t.row0 > top ? top : t.row0);
     t.n0 = nt * BN;
     const int ntop = g.N > BN ? g.N - BN : 0;
     t.n_base = t.n0 > ntop ? ntop : t.n0;
@@ -522,6 +529,83 @@ __device__ __forceinline__ int tile_row_limit(const GroupedGemm& g, const TileGe
     if (t.row_base != t.row0) return lim;
     const int64_t valid = t.row_end - t.row0;
     return valid >= 1 && valid - 1 < lim ? static_cast<int>(valid - 1) : lim;
+}
+
+// Epilogue of one row of 32 x 32 blocks: rows [row, row + 32) of the wave (row: buffer row of
+// the block's first), NI blocks of columns from n_lo, accumulators acc[nb][j].  kUp: bf16 H,
+// K-blocked; otherwise row-major C (bf16 or fp32), with `scatter` w[t] * row into row
+// t = scatter[row]; with `part` plain fp32 sums to partial[row][N].  Rows outside
+// [row_lo, t.row_end) and columns outside [t.n0, N) are not stored.
+template <int EPI, bool OB, int NB, int NI, bool IN_AGPR, typename Acc>
+__device__ __forceinline__ void store_row_block(const GroupedGemm& g, const TileGeom& t, int64_t row, int n_lo,
+                                                float* part, const Acc& acc) {
+    constexpr bool kUp = EPI != kEpiNone;
+    const int lane = threadIdx.x & 63;
+    const int64_t row_lo = t.row0 > 0 ? t.row0 : 0;
+    int64_t r0 = row + (lane & 15), r1 = r0 + 16;  // the rows this lane stores
+    const bool ok0 = r0 >= row_lo && r0 < t.row_end, ok1 = r1 >= row_lo && r1 < t.row_end;
+    float scale = 1.f;
+    if (!kUp && g.scatter && !part) {
+        // the grouped row's token and gate weight: looked up for the row whose sums this lane
+        // holds (row + l % 32), then handed to the lanes that store it
+        const int64_t rs = row + (lane & 31);
+        const bool ok = rs >= row_lo && rs < t.row_end;
+        const int64_t src = ok ? g.scatter[rs] : 0;
+        const int tok = static_cast<int>(src < 0 ? 0 : (src >= g.c_rows ? g.c_rows - 1 : src));
+        scale = ok ? g.scatter_w[tok] : 0.f;
+        r0 = __shfl(tok, lane & 15, 64);
+        r1 = __shfl(tok, 16 + (lane & 15), 64);
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int cb = n_lo + j * 32;  // the block's first column
+        if (OB && !part) {
+            uint2 pk[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    v[c] = epilogue_fast<EPI>(acc_read<IN_AGPR>(acc[0][j][4 * q + c]),
+                                              acc_read<IN_AGPR>(acc[NB - 1][j][4 * q + c]));
+                if (!kUp)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] *= scale;
+                pk[q].x = pack_bf16x2(v[0], v[1]);
+                pk[q].y = pack_bf16x2(v[2], v[3]);
+            }
+            // runs of 8 columns: inside one 32-column block of K-blocked H (N, n0 and cb are
+            // multiples of 32 there) or inside a row of y (N, n0 and cb are multiples of 8),
+            // wholly before n0 or wholly after it
+            const int col = cb + store_col_bf16(lane);
+            const bool okc = col >= t.n0 && col < g.N;
+            bf16_t* const C = static_cast<bf16_t*>(g.c);
+            const int64_t hb = (static_cast<int64_t>(cb) >> 5) * g.rows_max;
+            bf16_t* const d0 = C + (kUp ? (hb + r0) * 32 + (col & 31) : r0 * g.ldc + col);
+            bf16_t* const d1 = C + (kUp ? (hb + r1) * 32 + (col & 31) : r1 * g.ldc + col);
+            store_block_bf16(d0, d1, pk, ok0 && okc, ok1 && okc);
+        } else {
+            // fp32: groups of 4 columns, N % 4 == 0
+            float* const C = part ? part : static_cast<float*>(g.c);
+            const int64_t ld = part ? g.N : g.ldc;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                float u[4], v[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    u[c] = scale * acc_read<IN_AGPR>(acc[0][j][8 * p + c]);
+                    v[c] = scale * acc_read<IN_AGPR>(acc[0][j][8 * p + 4 + c]);
+                }
+                const int col = cb + 16 * p + store_col_f32(lane);
+                const bool okc = col >= t.n0 && col < g.N;
+                store_block_f32(C + r0 * ld + col, C + r1 * ld + col, u, v, ok0 && okc, ok1 && okc);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // one block at a time: keeps the scheduler from pulling every accumulator into VGPRs
+        // at once
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 // Persistent grouped GEMM.  The grid is a fixed number of workgroups (one or two per CU);
@@ -597,7 +681,7 @@ void gemm_bf16_lds(GroupedGemm g) {
     int lt = t_first, lk = 0;
     const unsigned char *src_a = nullptr, *src_b0 = nullptr, *src_b1 = nullptr;
     auto set_tile = [&](int L) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, total_m, L / ks);
+        const TileGeom t = tile_geom<BM, BN>(g, tiles, L / ks);
         const int64_t k0 = static_cast<int64_t>(L % ks) * nk;  // first K block of the work item
         const int64_t rb = kUp ? 2 * static_cast<int64_t>(g.K) : 64;
         if (kUp && g.gather) {
@@ -683,7 +767,7 @@ void gemm_bf16_lds(GroupedGemm g) {
     constexpr bool kAccInAgpr = S::kPerCU == 1;
     int consumed = 0;
     for (int ct = t_first; ct < t_end; ct += nslot) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, total_m, ct / ks);
+        const TileGeom t = tile_geom<BM, BN>(g, tiles, ct / ks);
         // Row blocks of this wave that hold valid rows.  Valid rows start at the tile's first
         // row unless the tile was shifted back at the end of the buffer; then all count.  The
         // count is rounded up to MI / 2 or MI so that three loop bodies cover every case.
@@ -694,7 +778,7 @@ void gemm_bf16_lds(GroupedGemm g) {
         }
         nv = __builtin_amdgcn_readfirstlane(nv);
 
-        f32x16_t acc[NB][MI][NI];
+        f32x16_t acc[MI][NB][NI];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -702,7 +786,7 @@ void gemm_bf16_lds(GroupedGemm g) {
 #pragma unroll
                 for (int j = 0; j < NI; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[nb][i][j][r] = 0.f;
+                    for (int r = 0; r < 16; ++r) acc[i][nb][j][r] = 0.f;
 
         // publish the tile's first stage; after an epilogue its stores share the counter
         if (ct != t_first) wait_vmcnt<0>();
@@ -722,8 +806,8 @@ void gemm_bf16_lds(GroupedGemm g) {
                     for (int j = 0; j < NI; ++j)
 #pragma unroll
                         for (int i = 0; i < NV; ++i)
-                            acc[nb][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[MI + nb * NI + j], f[i],
-                                                                                    acc[nb][i][j], 0, 0, 0);
+                            acc[i][nb][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[MI + nb * NI + j], f[i],
+                                                                                    acc[i][nb][j], 0, 0, 0);
             };
             Frags f0, f1;
             read_frags(nv_tag, consumed % NS, 0, f0);
@@ -756,95 +840,14 @@ void gemm_bf16_lds(GroupedGemm g) {
         else if (nv > 0) k_loop(std::integral_constant<int, MI / 2>());
         else k_loop(std::integral_constant<int, 0>());
 
-        // ---- epilogue of tile ct.  D[n][m] layout: lane holds activation row l32 of the
-        // block; register r holds weight row 8 * (r / 4) + 4 * lhi + r % 4, i.e. 4
-        // consecutive output columns per group r / 4.  bf16 output: two 16-byte runs per
-        // lane and block (store_block_bf16); fp32 output: the four groups as 16-byte vectors,
-        // 8 elements apart from the lane's address (immediate store offsets).
-        const int64_t row_lo = t.row0 > 0 ? t.row0 : 0;
-        if (ks > 1) {
-            // a K part: its fp32 sums go to partial[part][row][N], the reduce kernel finishes
-            float* const part = g.partial + static_cast<int64_t>(ct % ks) * g.rows_max * g.N;
-#pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                if (i >= nv) break;
-                const int64_t row = t.row_base + wm * (BM / 2) + i * 32 + l32;
-                const bool row_ok = row >= row_lo && row < t.row_end;
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    const int col0 = t.n_base + wn * (BN / WN) + j * 32 + 4 * lhi;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int col = col0 + 8 * q;
-                        if (row_ok && col >= t.n0 && col < g.N)
-                            *reinterpret_cast<float4*>(part + row * g.N + col) =
-                                make_float4(acc_read<kAccInAgpr>(acc[0][i][j][4 * q]),
-                                            acc_read<kAccInAgpr>(acc[0][i][j][4 * q + 1]),
-                                            acc_read<kAccInAgpr>(acc[0][i][j][4 * q + 2]),
-                                            acc_read<kAccInAgpr>(acc[0][i][j][4 * q + 3]));
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-            }
-            continue;
-        }
+        // ---- epilogue of tile ct; a K part's fp32 sums go to partial[part][row][N], the
+        // reduce kernel finishes
+        float* const part = !kUp && ks > 1 ? g.partial + static_cast<int64_t>(ct % ks) * g.rows_max * g.N : nullptr;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             if (i >= nv) break;  // no valid row in this block or any later one
-            int64_t row = t.row_base + wm * (BM / 2) + i * 32 + l32;
-            const bool row_ok = row >= row_lo && row < t.row_end;
-            float scale = 1.f;
-            if (!kUp && g.scatter) {
-                // the grouped row's token and gate weight (one index load per tile and row)
-                const int64_t src = row_ok ? g.scatter[row] : 0;
-                row = src < 0 ? 0 : (src >= g.c_rows ? g.c_rows - 1 : src);
-                scale = row_ok ? g.scatter_w[row] : 0.f;
-            }
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                const int cb = t.n_base + wn * (BN / WN) + j * 32;  // the block's first column
-                if constexpr (OB) {
-                    uint2 pk[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float v[4];
-#pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            v[c] = scale * epilogue_fast<EPI>(acc_read<kAccInAgpr>(acc[0][i][j][4 * q + c]),
-                                                              acc_read<kAccInAgpr>(acc[NB - 1][i][j][4 * q + c]));
-                        pk[q].x = pack_bf16x2(v[0], v[1]);
-                        pk[q].y = pack_bf16x2(v[2], v[3]);
-                    }
-                    // runs of 8 columns from c0 and c0 + 16: inside one 32-column block of
-                    // K-blocked H (N, n0 and cb are multiples of 32 there), or inside a row of
-                    // y (N, n0 and cb are multiples of 8), wholly before n0 or wholly after it
-                    const int c0 = cb + 8 * lhi;
-                    bf16_t* const dst = static_cast<bf16_t*>(g.c) +
-                                        (kUp ? ((static_cast<int64_t>(cb) >> 5) * g.rows_max + row) * 32 + 8 * lhi
-                                             : row * g.ldc + c0);
-                    store_block_bf16(dst, pk, row_ok && c0 >= t.n0 && c0 < g.N,
-                                     row_ok && c0 + 16 >= t.n0 && c0 + 16 < g.N);
-                } else {
-                    // fp32 y_perm (down-projection): groups of 4 columns, N % 4 == 0
-                    const int col0 = cb + 4 * lhi;
-                    float* const dst = static_cast<float*>(g.c) + row * g.ldc + col0;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int col = col0 + 8 * q;
-                        float v[4];
-#pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            v[c] = scale * epilogue_fast<EPI>(acc_read<kAccInAgpr>(acc[0][i][j][4 * q + c]),
-                                                              acc_read<kAccInAgpr>(acc[NB - 1][i][j][4 * q + c]));
-                        if (row_ok && col >= t.n0 && col < g.N)
-                            *reinterpret_cast<float4*>(dst + 8 * q) = make_float4(v[0], v[1], v[2], v[3]);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                // one block at a time: keeps the scheduler from pulling every accumulator
-                // into VGPRs at once
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            store_row_block<EPI, OB, NB, NI, kAccInAgpr>(g, t, t.row_base + wm * (BM / 2) + i * 32,
+                                                         t.n_base + wn * (BN / WN), part, acc[i]);
         }
     }
 }
@@ -890,7 +893,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lds0 = lds_address(smem_raw);
-    const int a_lim = static_cast<int>(g.rows_max < BM ? g.rows_max : BM) - 1;
     const int b_lim = (g.N < BN ? g.N : BN) - 1;
 
     // B: load j fills B rows (4 j + wave) 16 + lane / 4 of a stage, slot lane % 4, with global
@@ -909,7 +911,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
     int lt = t_first, lk = 0;
     const unsigned char *src_a = nullptr, *src_b0 = nullptr, *src_b1 = nullptr;
     auto set_tile = [&](int L) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, total_m, L);
+        const TileGeom t = tile_geom<BM, BN>(g, tiles, L);
 #pragma unroll
         for (int j = 0; j < LPA; ++j) {
             const int R = (j * 4 + wave) * 8 + (lane >> 3);
@@ -985,7 +987,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
 
     int consumed = 0;
     for (int ct = t_first; ct < t_end; ct += nslot) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, total_m, ct);
+        const TileGeom t = tile_geom<BM, BN>(g, tiles, ct);
         int nv = MI;
         if (t.row_base == t.row0) {
             const int64_t left = t.row_end - (t.row0 + wm * (BM / 2));
@@ -993,7 +995,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
         }
         nv = __builtin_amdgcn_readfirstlane(nv);
 
-        f32x16_t acc[NB][MI][NI];
+        f32x16_t acc[MI][NB][NI];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -1001,7 +1003,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
 #pragma unroll
                 for (int j = 0; j < NI; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[nb][i][j][r] = 0.f;
+                    for (int r = 0; r < 16; ++r) acc[i][nb][j][r] = 0.f;
 
         // publish the tile's first stage; after an epilogue its stores share the counter
         if (ct != t_first) wait_vmcnt<0>();
@@ -1018,8 +1020,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
                     for (int j = 0; j < NI; ++j)
 #pragma unroll
                         for (int i = 0; i < NV; ++i)
-                            acc[nb][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[MI + nb * NI + j], f[i],
-                                                                                    acc[nb][i][j], 0, 0, 0);
+                            acc[i][nb][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[MI + nb * NI + j], f[i],
+                                                                                    acc[i][nb][j], 0, 0, 0);
             };
             Frags f0, f1;
             read_frags(nv_tag, consumed, 0, f0);
@@ -1050,33 +1052,234 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
         else k_loop(std::integral_constant<int, 0>());
 
         // epilogue: as in gemm_bf16_lds (bf16 H, K-blocked)
-        const int64_t row_lo = t.row0 > 0 ? t.row0 : 0;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             if (i >= nv) break;
-            const int64_t row = t.row_base + wm * (BM / 2) + i * 32 + l32;
-            const bool row_ok = row >= row_lo && row < t.row_end;
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                const int cb = t.n_base + wn * (BN / 2) + j * 32;  // the block's first column
-                uint2 pk[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float v[4];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        v[c] = epilogue_fast<EPI>(acc[0][i][j][4 * q + c], acc[NB - 1][i][j][4 * q + c]);
-                    pk[q].x = pack_bf16x2(v[0], v[1]);
-                    pk[q].y = pack_bf16x2(v[2], v[3]);
-                }
-                bf16_t* const dst = static_cast<bf16_t*>(g.c) +
-                                    ((static_cast<int64_t>(cb) >> 5) * g.rows_max + row) * 32 + 8 * lhi;
-                const bool ok = row_ok && cb >= t.n0 && cb < g.N;  // N, n0, cb: multiples of 32
-                store_block_bf16(dst, pk, ok, ok);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            store_row_block<EPI, true, NB, NI, false>(g, t, t.row_base + wm * (BM / 2) + i * 32,
+                                                      t.n_base + wn * (BN / 2), nullptr, acc[i]);
         }
     }
+}
+
+// ------------------------------------------------------------------ bf16 MFMA kernel, two wave groups in turn
+//
+// For calls whose experts have many rows (which calls: turns_up, turns_down below), where the
+// matrix cores are the bound.  256 x 256 tiles (SwiGLU: 128 columns of W1 and the same of W3),
+// eight waves in one workgroup per CU: per product two thirds of the LDS fills (and so of the
+// L2 reads) of the 128 x 256 tiles above.  K advances 32 at a time through a ring of four
+// 32 KiB stages, three in flight.
+//
+// The waves form two groups of four, one wave of each group per SIMD.  Group r multiplies the
+// tile's odd or even 32-row blocks (so that a tile with few rows still feeds both), wave w of
+// it columns 64 w .. 64 w + 63.  The groups take turns: while one runs a stage's 16 MFMAs, the
+// other reads its fragments of a stage and issues its share of the loads.  Left to themselves
+// both waves of a SIMD read at the same time and then multiply at the same time.  Turns are
+// separated by barriers of the whole workgroup; group 1 starts one barrier late.  In turns
+// t = 0, 1, ..: group 0 reads stage s in turn 2 s and multiplies it in turn 2 s + 1, group 1
+// each one turn later.  So stage s has to be in LDS at the end of turn 2 s - 1: there each wave
+// waits for its own loads of it (group 0 after its MFMAs, group 1 after its reads).  Stage s's
+// buffer has been read by the end of turn 2 s + 1 and is refilled in each group's reading turn
+// of stage s + 1.
+//
+// Measured, 65536 rows in two experts (x 1024 -> 4096 -> 1024, GELU): down-projection 430 us,
+// 1.28 PFLOP/s, and 349 us on zeros, so the rest is power; the 128 x 256 tiles take 521 us.
+// The up-projection's epilogue (16 k cycles of vector work a tile and SIMD) has nothing to
+// overlap with here, so that short K loops stay with gemm_up_pairs.
+constexpr int kTurnStages = 4;
+constexpr size_t kTurnBytes = static_cast<size_t>(kTurnStages) * 512 * 64;
+
+template <int EPI, bool OB>
+__global__ __launch_bounds__(512, 2) void gemm_turns(GroupedGemm g) {
+    constexpr bool kUp = EPI != kEpiNone;
+    constexpr int BM = 256, BW = 256, NS = kTurnStages;
+    constexpr int NB = EPI == kEpiSwiglu ? 2 : 1;
+    constexpr int BN = BW / NB;           // output columns per tile
+    constexpr int MI = 4, NI = 2 / NB;    // 32-row / 32-column blocks per wave (and matrix)
+    constexpr int LPW = 4;                // 1 KiB loads per wave and stage: two of A, two of B
+    constexpr int kStageBytes = (BM + BW) * 64;
+    extern __shared__ __align__(1024) unsigned char smem_raw[];
+
+    RegTiles<BM> tiles;
+    tiles.build(g.offsets, g.E);
+    // This XCD's tiles [t_begin, t_end), dealt round-robin to its workgroups.  A last round
+    // that leaves most of them idle is cut finer: its `rest` tiles as `parts` items each, by rows.
+    const int total = tiles.total * g.n_tiles, per = (total + 7) >> 3;
+    const int xcd = blockIdx.x & 7, nslot = gridDim.x >> 3;
+    const int t_begin = min(total, xcd * per), t_end = min(total, t_begin + per);
+    const int rest = (t_end - t_begin) % nslot;
+    const int parts = rest * 4 <= nslot ? 4 : (rest * 2 <= nslot ? 2 : 1);
+    const int whole = t_end - t_begin - rest, items = whole + rest * parts;
+    const int i_first = static_cast<int>(blockIdx.x >> 3);
+    if (i_first >= items) return;
+    auto item_geom = [&](int i) {
+        if (i < whole) return tile_geom<BM, BN>(g, tiles, t_begin + i);
+        const int r = (i - whole) / parts, p = i - whole - r * parts;
+        TileGeom t = tile_geom<BM, BN>(g, tiles, t_begin + whole + r);
+        if (parts > 1) {
+            // rows [p q, (p + 1) q) of the tile's valid ones, q a multiple of 32
+            const int64_t valid = t.row_end - t.row0 < BM ? t.row_end - t.row0 : BM;
+            const int64_t q = (valid + 32 * parts - 1) / (32 * parts) * 32;
+            const int64_t end = t.row0 + (p + 1) * q;
+            t.row0 += p * q;
+            t.row_end = end < t.row_end ? end : t.row_end;
+            const int64_t top = g.rows_max > BM ? g.rows_max - BM : 0;
+            t.row_base = t.row0 > top ? top : t.row0;
+        }
+        return t;
+    };
+    const int nk = g.K / 32;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t lds0 = lds_address(smem_raw);
+    const int b_lim = (g.N < BN ? g.N : BN) - 1;
+
+    // load j of a stage fills LDS rows (8 j + wave) 16 + lane / 4, slot lane % 4, with global
+    // chunk slot ^ ((row / 4) % 4)
+    uint32_t voff[LPW];
+    const int r_lane = lane >> 2;
+    const uint32_t kc16 = static_cast<uint32_t>(((lane & 3) ^ ((r_lane >> 2) & 3)) * 16);
+#pragma unroll
+    for (int j = 2; j < LPW; ++j) {
+        const int R = ((j - 2) * 8 + wave) * 16 + r_lane;
+        voff[j] = static_cast<uint32_t>(min(R % BN, b_lim)) * 64u + kc16;
+    }
+
+    int li = i_first, lk = 0;
+    TileGeom lg;  // of the item being loaded
+    const unsigned char *src_a = nullptr, *src_b0 = nullptr, *src_b1 = nullptr;
+    auto set_item = [&](int i) {
+        lg = item_geom(i);
+        const TileGeom& t = lg;
+        const int a_lim = tile_row_limit<BM>(g, t);
+        const uint32_t rb = kUp ? static_cast<uint32_t>(2 * g.K) : 64u;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int R = min((j * 8 + wave) * 16 + r_lane, a_lim);
+            const int64_t r = (kUp && g.gather) ? source_row(g, t.row_base + R) : R;
+            voff[j] = static_cast<uint32_t>(r) * rb + kc16;
+        }
+        src_a = uniform_ptr(static_cast<const unsigned char*>(g.a) +
+                            ((kUp && g.gather) ? 0 : t.row_base * static_cast<int64_t>(rb)));
+        const int64_t boff = (t.e * g.b_estride) * 2 + static_cast<int64_t>(t.n_base) * 64;
+        src_b0 = uniform_ptr(static_cast<const unsigned char*>(g.b) + boff);
+        src_b1 = NB > 1 ? uniform_ptr(static_cast<const unsigned char*>(g.b2) + boff) : src_b0;
+    };
+    int issued = 0, slot_w = 0;  // stages issued so far; their ring slot
+    const int64_t a_step = kUp ? 64 : g.rows_max * 64, b_step = static_cast<int64_t>(g.N) * 64;
+    auto issue_next = [&]() {
+        if (li >= items) return;
+        const uint32_t dst = lds0 + slot_w * kStageBytes + wave * 1024;
+        load_lds16(src_a, voff[0], dst);
+        load_lds16(src_a, voff[1], dst + 8 * 1024);
+        load_lds16(src_b0, voff[2], dst + 16 * 1024);
+        load_lds16(NB > 1 ? src_b1 : src_b0, voff[3], dst + 24 * 1024);
+        src_a += a_step;
+        src_b0 += b_step;
+        if (NB > 1) src_b1 += b_step;
+        ++issued;
+        slot_w = slot_w + 1 == NS ? 0 : slot_w + 1;
+        if (++lk == nk) {
+            lk = 0;
+            li += nslot;
+            if (li < items) set_item(li);
+        }
+    };
+    set_item(li);
+#pragma unroll
+    for (int st = 0; st < NS - 1; ++st) issue_next();
+
+    const int grp = wave >> 2, wn = wave & 3;
+    const int l32 = lane & 31, lhi = lane >> 5;
+    // a fragment's byte offset inside its 32 LDS rows: K chunk 2 ks + lhi of row l32
+    const uint32_t f0 = static_cast<uint32_t>(l32 * 64 + ((lhi ^ ((l32 >> 2) & 3)) << 4));
+    const uint32_t f1 = static_cast<uint32_t>(l32 * 64 + (((2 + lhi) ^ ((l32 >> 2) & 3)) << 4));
+
+    int consumed = 0, slot_r = 0;
+    wait_stages<LPW, NS>(issued - 1);
+    stage_barrier();
+    if (grp == 1) stage_barrier();
+    for (int ci = i_first; ci < items; ci += nslot) {
+        // the loads are NS - 1 stages ahead: still in this item unless it is that short
+        const TileGeom t = nk >= NS ? lg : item_geom(ci);
+        int nv = MI;
+        if (t.row_base == t.row0) {
+            const int64_t left = t.row_end - t.row0 - 32 * grp;
+            nv = left <= 0 ? 0 : (left >= BM - 64 ? MI : static_cast<int>((left + 63) >> 6));
+        }
+        nv = __builtin_amdgcn_readfirstlane(nv);
+
+        f32x16_t acc[MI][NB][NI];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][nb][j][r] = 0.f;
+
+        auto k_loop = [&](auto nv_tag) {
+            constexpr int NV = decltype(nv_tag)::value;
+            for (int ck = 0; ck < nk; ++ck) {
+                // ---- memory turn
+                bf16x8_t fa[2][MI], fb[2][2];
+                const unsigned char* sa = smem_raw + slot_r * kStageBytes + grp * 32 * 64;
+                const unsigned char* sb = smem_raw + slot_r * kStageBytes + BM * 64 + wn * (64 / NB) * 64;
+                if (NV > 0) {
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks) {
+                        const uint32_t f = ks ? f1 : f0;
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            fb[ks][j] = *reinterpret_cast<const bf16x8_t*>(sb + f + (NB > 1 ? j * BN * 64 : j * 32 * 64));
+#pragma unroll
+                        for (int i = 0; i < NV; ++i)
+                            fa[ks][i] = *reinterpret_cast<const bf16x8_t*>(sa + f + i * 64 * 64);
+                    }
+                }
+                issue_next();
+                ++consumed;
+                slot_r = slot_r + 1 == NS ? 0 : slot_r + 1;
+                wait_lgkm0();
+                if (grp == 1) wait_stages<LPW, NS>(issued - consumed - 1);
+                __builtin_amdgcn_sched_barrier(0);
+                stage_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+                // ---- matrix turn
+                if (NV > 0) {
+                    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+#pragma unroll
+                            for (int i = 0; i < NV; ++i) {
+                                f32x16_t& a = acc[i][NB > 1 ? j : 0][NB > 1 ? 0 : j];
+                                a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks][i], a, 0, 0, 0);
+                            }
+                    __builtin_amdgcn_s_setprio(0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (grp == 0) wait_stages<LPW, NS>(issued - consumed - 1);
+                stage_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (nv == MI) k_loop(std::integral_constant<int, MI>());
+        else if (nv == 3) k_loop(std::integral_constant<int, 3>());
+        else if (nv == 2) k_loop(std::integral_constant<int, 2>());
+        else if (nv == 1) k_loop(std::integral_constant<int, 1>());
+        else k_loop(std::integral_constant<int, 0>());
+
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            if (i >= nv) break;
+            store_row_block<EPI, OB, NB, NI, false>(g, t, t.row_base + (2 * i + grp) * 32, t.n_base + wn * (BN / 4),
+                                                    nullptr, acc[i]);
+        }
+    }
+    if (grp == 0) stage_barrier();
 }
 
 // ------------------------------------------------------------------ fp32 kernel
@@ -1316,7 +1519,7 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
     int li = t_first, lk = 0;
     const unsigned char *src_a = nullptr, *src_b0 = nullptr, *src_b1 = nullptr;
     auto set_item = [&](int L) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, total_m, L / ks);
+        const TileGeom t = tile_geom<BM, BN>(g, tiles, L / ks);
         const int64_t k0 = static_cast<int64_t>(L % ks) * nk * kF2BK;  // first K value of the item
         if (g.gather) {
             // absolute source row (T h 4 < 4 GiB is checked by the host)
@@ -1355,7 +1558,7 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
     const int l32 = lane & 31, lhi = lane >> 5;
     int consumed = 0;
     for (int L = t_first; L < t_end; L += nslot) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, total_m, L / ks);
+        const TileGeom t = tile_geom<BM, BN>(g, tiles, L / ks);
         f32x16_t acc[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
@@ -1679,6 +1882,37 @@ hipError_t run_up_pairs(GroupedGemm g, int64_t A_max, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Which launches take gemm_turns, from the sizes the host knows.  Measured over A = 3000 ..
+// 65536 rows, 8 .. 64 experts, K = 512 .. 4096 (us, the 128 x 256 tiles against 256 x 256):
+// down-projection: K = 4096 545 / 491 (1024 rows per expert), 302 / 288 (512), 213 / 210 (256);
+//   K = 2816 67 / 64 (188); K = 1792 140 / 138; but K = 1024 28 / 27 (128), K = 512 37 / 44 (512):
+//   a short K loop does not pay for its fill and the single workgroup's exposed epilogue;
+// up-projection: K = 4096 941 / 799, 369 / 307, 262 / 219 and, in less than one round of tiles,
+//   141 / 124, but 137 / 173 where the tiles are just over one round of the CUs; K = 2048
+//   419 / 378 over many rounds, a tie below; K = 1024 702 / 708.
+bool turns_rows(int64_t A_max, int E) { return A_max >= 192 * static_cast<int64_t>(E); }
+bool turns_down(const GroupedGemm& g, int64_t A_max) { return g.K >= 1536 && turns_rows(A_max, g.E); }
+bool turns_up(const GroupedGemm& g, int64_t A_max, int n_tiles) {
+    if (g.K % 32 != 0 || g.K < 1536 || !turns_rows(A_max, g.E)) return false;
+    // expected rounds of tiles: half an empty row tile per expert
+    const double rounds = (static_cast<double>(A_max) / 256 + 0.5 * g.E) * n_tiles / device_cus();
+    return rounds >= 4 || (g.K >= 3072 && (rounds >= 1.6 || (rounds <= 1 && rounds >= 0.75)));
+}
+
+template <int EPI, bool OB>
+hipError_t run_turns(GroupedGemm g, int64_t A_max, hipStream_t s) {
+    static const hipError_t attr =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_turns<EPI, OB>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kTurnBytes));
+    if (attr != hipSuccess) return attr;
+    g.n_tiles = static_cast<int>(ceil_div(g.N, EPI == kEpiSwiglu ? 128 : 256));
+    const int64_t tiles = row_tile_bound(A_max, g.E, 256) * g.n_tiles;
+    if (tiles == 0) return hipSuccess;
+    const int64_t blocks = round_up(std::min<int64_t>(tiles, device_cus()), 8);
+    hipLaunchKernelGGL((gemm_turns<EPI, OB>), dim3(static_cast<unsigned>(blocks)), dim3(512), kTurnBytes, s, g);
+    return hipGetLastError();
+}
+
 template <int EPI, bool OB>
 hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
     constexpr bool kUp = EPI != kEpiNone;
@@ -1689,6 +1923,8 @@ hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
         // a 64-token top-2 step: about 10 us less than 128 x 256, 1.6 us less than 128 x 128;
         // no gain from 256 rows up, where the tiles already cover the CUs).
         if (A_max <= 128 && g.K % 32 == 0) return run_bf16_lds<64, 128, 32, 3, EPI, OB>(g, A_max, s);
+        if (turns_up(g, A_max, static_cast<int>(ceil_div(g.N, EPI == kEpiSwiglu ? 128 : 256))))
+            return run_turns<EPI, OB>(g, A_max, s);
         // activation rows in 128-byte pieces when K allows it (see gemm_up_pairs)
         if constexpr (OB) {
             if (g.K % 64 == 0) return run_up_pairs<EPI>(g, A_max, s);
@@ -1699,6 +1935,7 @@ hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
         if (g.K % 32 != 0) return hipErrorInvalidValue;  // not reachable through the C ABI (fp % 128 == 0)
         if (g.ksplit > 1 && A_max <= 128) return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
         if (g.ksplit > 1) return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);
+        if (turns_down(g, A_max)) return run_turns<EPI, OB>(g, A_max, s);
         if (g.N >= 384 && row_tile_bound(A_max, g.E, 128) * ceil_div(g.N, 384) <= device_cus())
             return run_bf16_lds<128, 384, 32, 3, EPI, OB, 4>(g, A_max, s);
         return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);

@@ -295,6 +295,50 @@ def test_ffn_parity_on_random_shapes(i, counts, h, f, act, dtype):
         assert rowwise(got, ref) <= TOL[dtype], (rowwise(got, ref), normwise(got, ref))
 
 
+@pytest.mark.parametrize("act", ["gelu", "gelu_tanh", "swiglu"])
+@pytest.mark.parametrize("counts,h,f", [
+    ([600], 72, 1536),                # down-projection on 256 x 256 tiles: N below one tile
+    ([513, 31, 800, 1], 264, 1600),   # N just over a tile; last row tiles of 1, 31 and 32 rows
+    ([256, 768], 776, 1700),          # whole row tiles, N = 3 tiles and 8 columns
+    ([1023], 3072, 12200),            # up-projection too (K = 3072: 0.84 rounds of tiles, SwiGLU 1.7)
+    ([1500, 700], 1536, 16900),       # ... K = 1536, 5 rounds for SwiGLU
+])
+def test_wide_tiles_match_128_row_tiles(act, counts, h, f):
+    """256 x 256 tiles sum every output in the same order as the 128-row tiles: the call with
+    rows enough per expert for them equals, bit for bit, the same rows in a call with so many
+    empty experts beside them that it takes the 128-row tiles.  fp32, bf16 and top-1 outputs."""
+    A, E, dev = sum(counts), len(counts), "cuda"
+    pad = A // 192 + 1 - E  # empty experts that bring the rows per expert below 192
+    assert A >= 192 * E and pad > 0
+    g = torch.Generator(device=dev).manual_seed(A + h + f)
+    n = lambda *shape: torch.randn(shape, generator=g, device=dev).mul_(0.05).bfloat16()  # noqa: E731
+    x, w1, w2 = n(A, h) * 20, n(E, h, f), n(E, f, h)
+    w3 = n(E, h, f) if act == "swiglu" else None
+    grow = lambda w: None if w is None else torch.cat([w, w[:1].expand(pad, -1, -1)]).contiguous()  # noqa: E731
+    off = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device=dev)
+    off2 = torch.cat([off, off[-1:].expand(pad)]).contiguous()
+    perm = torch.randperm(A, generator=g, device=dev).int()
+    wt = torch.rand(A, generator=g, device=dev)
+    outs = []
+    for o, args in ((off, (w1, w2, w3)), (off2, (grow(w1), grow(w2), grow(w3)))):
+        packed = moe.pack_weights(*args, act=act)
+        outs.append((moe.expert_ffn_shard(x, o, packed), moe.expert_ffn_shard(x, o, packed, out_dtype=torch.float32),
+                     moe.expert_ffn_shard_top1(x, perm, wt, o, packed)))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    ref = outs[0][1].double()
+    want = torch.empty_like(ref)
+    for e in range(E):
+        r = slice(int(off[e]), int(off[e + 1]))
+        u = x[r].float() @ w1[e].float()
+        if act == "swiglu":
+            u = torch.nn.functional.silu(u) * (x[r].float() @ w3[e].float())
+        else:
+            u = torch.nn.functional.gelu(u, approximate="tanh" if act == "gelu_tanh" else "none")
+        want[r] = (u @ w2[e].float()).double()
+    assert float(((ref - want).abs().amax(1) / want.abs().amax(1)).max()) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
 @pytest.mark.parametrize("A,f", [(3000, 128), (300, 1024)])
