@@ -149,9 +149,8 @@ moe_status moe_pack_weights(const void *w1, const void *w3, const void *w2, int3
                             hipStream_t stream);
 
 /* Bytes of workspace moe_expert_ffn_shard needs: the activated inner rows (A_max x fp) and,
- * for bf16, room for fp32 partial sums of the second product (at most 2048 x h floats):
- * calls with A_max <= 512 split its K into up to 8 parts so that few rows still occupy
- * the whole GPU.  Non-decreasing in A_max, so a workspace sized for a bound serves every
+ * room for fp32 sums of the second product that a small call hands to the combine (at most
+ * 2048 x h floats for bf16, 4096 x h for fp32).  Non-decreasing in A_max, so a workspace sized for a bound serves every
  * call with a smaller A_max. */
 size_t moe_ffn_workspace_size(int64_t A_max, int32_t E, int64_t h, int64_t f, moe_act act,
                               moe_dtype dt);
@@ -161,10 +160,10 @@ size_t moe_ffn_workspace_size(int64_t A_max, int32_t E, int64_t h, int64_t f, mo
  *     y_perm[p] = act(x_perm[p] . W1_e^g) . W2_e^g        (shard g = the packed slice)
  * computed with bf16 MFMA and fp32 accumulation (dt = MOE_BF16) or fp32 arithmetic
  * (dt = MOE_F32).  The activated row is rounded to dt before the second product.  One
- * launch per matmul regardless of E; the per-expert counts are read on the device.  A small
- * bf16 call (A_max <= 512) sums the second product's K in parts, each part in fp32, the
- * parts added in a fixed order by one more launch; the split depends only on A_max and f,
- * so results are deterministic and every entry point agrees bit for bit on one call.
+ * launch per matmul regardless of E; the per-expert counts are read on the device.  A call
+ * with few rows per expert sums each product's K in parts, each part in fp32, the parts
+ * added in a fixed order; which calls do depends only on A_max, E, f and dt, so results are
+ * deterministic and every entry point agrees bit for bit on one call.
  *   x_perm  [A, h] dtype dt, grouped rows from moe_dispatch
  *   offsets [E+1] int32, device; offsets[E] must not exceed A_max
  *   A_max   host-known upper bound of offsets[E] (normally T*k); sizes the launch
@@ -192,15 +191,15 @@ moe_status moe_expert_ffn_shard_gather(const void *x, int64_t T, const int32_t *
 
 /* Steps 4 and 5 together for any k (Algorithm 1's expert computation and weighted
  * combination): moe_expert_ffn_shard_gather on rows_max = T * k followed by moe_combine,
- * with the same y bit for bit.  When the second product's K is split (calls of at most 512
- * bf16 or 1024 fp32 rows, the decode-sized ones), the parts' sum and the combine run as one
- * launch: each token's rows are summed over the parts, rounded to ydt exactly as y_perm
+ * with the same y bit for bit.  For the decode-sized calls (at most 512 bf16 or 1024
+ * fp32 rows, f not too short) the second product stays in fp32 sums in the workspace and the
+ * combine reads those: each token's rows are rounded to ydt exactly as y_perm
  * would hold them, weighted and accumulated in pick order, and y_perm is not written;
  * otherwise y_perm is written as by moe_expert_ffn_shard_gather and then combined.
  *   x, row_src, offsets, E, h, f, act, dt, packed, ydt, ws: as moe_expert_ffn_shard_gather
  *            with A_max = T * k (T * k < 2^31)
  *   pos_of   [T, k] int32 from moe_dispatch;  topk_w [T, k] fp32 from moe_route
- *   y_perm   [T * k, h] dtype ydt scratch (written only when K is not split)
+ *   y_perm   [T * k, h] dtype ydt scratch (written only by larger calls)
  *   y        [T, h] out, dtype out_dt
  *   y_perm_written  optional host int: set to 1 if y_perm was written, else 0 (may be NULL) */
 moe_status moe_expert_ffn_shard_gather_combine(const void *x, int64_t T, const int32_t *row_src,

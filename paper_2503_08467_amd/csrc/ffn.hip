@@ -10,17 +10,19 @@
 // the host-known bound A_max, at most as many workgroups per CU as LDS allows, a multiple
 // of the 8 XCDs), so the counts are never read back to the host.
 //
-// bf16 path (gemm_bf16_lds, gemm_up_pairs): 128-row tiles, 256 (or 384 / 128) weight rows
-// per tile, v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  Weights and H are stored
-// K-blocked (blocks of 32 K values, all rows side by side), so every stage of 32 K values
-// of a run of rows is one contiguous stretch that 1 KiB direct-to-LDS loads fetch; three
-// LDS stages, two in flight across K steps and tiles.  The epilogue applies the activation
-// in fp32, rounds once, and stores 16-byte runs straight from the accumulators (into
-// K-blocked H for GEMM1).  Calls of at most 512 rows split GEMM2's K into parts summed by
-// split_reduce (or, with the combine folded in, split_combine) in a fixed order.
-// fp32 path (gemm_f32_lds): 32 x 128 tiles on v_mfma_f32_32x32x2_f32, row-major operands in
-// 128-byte row pieces through two direct-to-LDS stages, three workgroups per CU; gemm_f32
-// (register-staged 64 x 64 tiles) only for an up-projection whose h is not a multiple of 32.
+// bf16, many rows per expert (gemm_bf16_lds, gemm_up_pairs, gemm_turns): 128- or 256-row
+// tiles, v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  Weights and H are stored K-blocked
+// (blocks of 32 K values, all rows side by side), so every stage of 32 K values of a run of
+// rows is one contiguous stretch that 1 KiB direct-to-LDS loads fetch; stages stay in flight
+// across K steps and tiles.  The epilogue applies the activation in fp32, rounds once, and
+// stores 16-byte runs straight from the accumulators (into K-blocked H for GEMM1).
+// Few rows per expert, both types (gemm_stream): K cut between a workgroup's waves, weights
+// streamed into registers.
+// fp32, many rows (gemm_f32_lds): 32 x 128 tiles on v_mfma_f32_32x32x2_f32, row-major operands
+// in 128-byte row pieces through two direct-to-LDS stages, three workgroups per CU; calls of
+// at most 1024 rows split GEMM2's K into parts summed by split_reduce (or, with the combine
+// folded in, split_combine) in a fixed order.  gemm_f32 (register-staged 64 x 64 tiles) only
+// for an up-projection whose h is not a multiple of 32.
 #include "common.h"
 #include "kernels.h"
 #include "lds_dma.h"
@@ -54,9 +56,9 @@ struct GroupedGemm {
     const int32_t* scatter;
     const float* scatter_w;
     int64_t c_rows;
-    // Down-projection only: with ksplit > 1 every tile is computed as ksplit parts of K/ksplit
-    // each, part s written in fp32 to partial[s][row][N] (no scale, no scatter); a reduce
-    // kernel sums the parts in order afterwards.
+    // Down-projection only: partial sums in fp32 to partial[s][row][N] (no scale, no scatter)
+    // for a kernel that adds the parts in order.  gemm_f32_lds: with ksplit > 1 every tile as
+    // ksplit parts of K / ksplit each.  gemm_stream: whole sums, one part.
     int ksplit;
     float* partial;
 };
@@ -534,18 +536,17 @@ __device__ __forceinline__ int tile_row_limit(const GroupedGemm& g, const TileGe
 // Epilogue of one row of 32 x 32 blocks: rows [row, row + 32) of the wave (row: buffer row of
 // the block's first), NI blocks of columns from n_lo, accumulators acc[nb][j].  kUp: bf16 H,
 // K-blocked; otherwise row-major C (bf16 or fp32), with `scatter` w[t] * row into row
-// t = scatter[row]; with `part` plain fp32 sums to partial[row][N].  Rows outside
-// [row_lo, t.row_end) and columns outside [t.n0, N) are not stored.
+// t = scatter[row].  Rows outside the tile's and columns outside [t.n0, N) are not stored.
 template <int EPI, bool OB, int NB, int NI, bool IN_AGPR, typename Acc>
 __device__ __forceinline__ void store_row_block(const GroupedGemm& g, const TileGeom& t, int64_t row, int n_lo,
-                                                float* part, const Acc& acc) {
+                                                const Acc& acc) {
     constexpr bool kUp = EPI != kEpiNone;
     const int lane = threadIdx.x & 63;
     const int64_t row_lo = t.row0 > 0 ? t.row0 : 0;
     int64_t r0 = row + (lane & 15), r1 = r0 + 16;  // the rows this lane stores
     const bool ok0 = r0 >= row_lo && r0 < t.row_end, ok1 = r1 >= row_lo && r1 < t.row_end;
     float scale = 1.f;
-    if (!kUp && g.scatter && !part) {
+    if (!kUp && g.scatter) {
         // the grouped row's token and gate weight: looked up for the row whose sums this lane
         // holds (row + l % 32), then handed to the lanes that store it
         const int64_t rs = row + (lane & 31);
@@ -559,7 +560,7 @@ __device__ __forceinline__ void store_row_block(const GroupedGemm& g, const Tile
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
         const int cb = n_lo + j * 32;  // the block's first column
-        if (OB && !part) {
+        if (OB) {
             uint2 pk[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -586,8 +587,7 @@ __device__ __forceinline__ void store_row_block(const GroupedGemm& g, const Tile
             store_block_bf16(d0, d1, pk, ok0 && okc, ok1 && okc);
         } else {
             // fp32: groups of 4 columns, N % 4 == 0
-            float* const C = part ? part : static_cast<float*>(g.c);
-            const int64_t ld = part ? g.N : g.ldc;
+            float* const C = static_cast<float*>(g.c);
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 float u[4], v[4];
@@ -598,7 +598,7 @@ __device__ __forceinline__ void store_row_block(const GroupedGemm& g, const Tile
                 }
                 const int col = cb + 16 * p + store_col_f32(lane);
                 const bool okc = col >= t.n0 && col < g.N;
-                store_block_f32(C + r0 * ld + col, C + r1 * ld + col, u, v, ok0 && okc, ok1 && okc);
+                store_block_f32(C + r0 * g.ldc + col, C + r1 * g.ldc + col, u, v, ok0 && okc, ok1 && okc);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -641,15 +641,13 @@ void gemm_bf16_lds(GroupedGemm g) {
 
     const int total_m = tile_prefix<BM>(g.offsets, g.E, tstart);
     const LdsTiles tiles{tstart, g.E};
-    // work item L = tile L / ks, K part L % ks (ks = 1 unless the down-projection is split)
-    const int ks = (!kUp && g.ksplit > 1) ? g.ksplit : 1;
-    const int total = total_m * g.n_tiles * ks;
+    const int total = total_m * g.n_tiles;
     const int per = (total + 7) >> 3;
     const int xcd = blockIdx.x & 7, nslot = gridDim.x >> 3;
     const int t_end = min(total, (xcd + 1) * per);
     const int t_first = xcd * per + static_cast<int>(blockIdx.x >> 3);
     if (t_first >= t_end) return;
-    const int nk = g.K / BK / ks;  // K steps per work item
+    const int nk = g.K / BK;
 
     const int tid = threadIdx.x, lane = tid & 63;
     // the wave index is uniform across a wave; say so, so that per-wave choices stay scalar
@@ -681,8 +679,7 @@ void gemm_bf16_lds(GroupedGemm g) {
     int lt = t_first, lk = 0;
     const unsigned char *src_a = nullptr, *src_b0 = nullptr, *src_b1 = nullptr;
     auto set_tile = [&](int L) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, L / ks);
-        const int64_t k0 = static_cast<int64_t>(L % ks) * nk;  // first K block of the work item
+        const TileGeom t = tile_geom<BM, BN>(g, tiles, L);
         const int64_t rb = kUp ? 2 * static_cast<int64_t>(g.K) : 64;
         if (kUp && g.gather) {
             // this lane's activation rows come from the gathered source rows (the index
@@ -706,10 +703,9 @@ void gemm_bf16_lds(GroupedGemm g) {
                 const int kc = c_lane ^ ((R >> SH) & (CPR - 1));
                 voff[j] = static_cast<uint32_t>(min(R, a_lim)) * static_cast<uint32_t>(rb) + static_cast<uint32_t>(kc * 16);
             }
-            src_a = uniform_ptr(static_cast<const unsigned char*>(g.a) + t.row_base * rb +
-                                (kUp ? 0 : k0 * g.rows_max * 64));
+            src_a = uniform_ptr(static_cast<const unsigned char*>(g.a) + t.row_base * rb);
         }
-        const int64_t boff = (t.e * g.b_estride) * 2 + static_cast<int64_t>(t.n_base) * 64 + k0 * g.N * 64;
+        const int64_t boff = (t.e * g.b_estride) * 2 + static_cast<int64_t>(t.n_base) * 64;
         src_b0 = uniform_ptr(static_cast<const unsigned char*>(g.b) + boff);
         src_b1 = NB > 1 ? uniform_ptr(static_cast<const unsigned char*>(g.b2) + boff) : src_b0;
     };
@@ -767,7 +763,7 @@ void gemm_bf16_lds(GroupedGemm g) {
     constexpr bool kAccInAgpr = S::kPerCU == 1;
     int consumed = 0;
     for (int ct = t_first; ct < t_end; ct += nslot) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, ct / ks);
+        const TileGeom t = tile_geom<BM, BN>(g, tiles, ct);
         // Row blocks of this wave that hold valid rows.  Valid rows start at the tile's first
         // row unless the tile was shifted back at the end of the buffer; then all count.  The
         // count is rounded up to MI / 2 or MI so that three loop bodies cover every case.
@@ -840,14 +836,12 @@ void gemm_bf16_lds(GroupedGemm g) {
         else if (nv > 0) k_loop(std::integral_constant<int, MI / 2>());
         else k_loop(std::integral_constant<int, 0>());
 
-        // ---- epilogue of tile ct; a K part's fp32 sums go to partial[part][row][N], the
-        // reduce kernel finishes
-        float* const part = !kUp && ks > 1 ? g.partial + static_cast<int64_t>(ct % ks) * g.rows_max * g.N : nullptr;
+        // ---- epilogue of tile ct
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             if (i >= nv) break;  // no valid row in this block or any later one
             store_row_block<EPI, OB, NB, NI, kAccInAgpr>(g, t, t.row_base + wm * (BM / 2) + i * 32,
-                                                         t.n_base + wn * (BN / WN), part, acc[i]);
+                                                         t.n_base + wn * (BN / WN), acc[i]);
         }
     }
 }
@@ -1056,7 +1050,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
         for (int i = 0; i < MI; ++i) {
             if (i >= nv) break;
             store_row_block<EPI, true, NB, NI, false>(g, t, t.row_base + wm * (BM / 2) + i * 32,
-                                                      t.n_base + wn * (BN / 2), nullptr, acc[i]);
+                                                      t.n_base + wn * (BN / 2), acc[i]);
         }
     }
 }
@@ -1276,7 +1270,7 @@ __global__ __launch_bounds__(512, 2) void gemm_turns(GroupedGemm g) {
         for (int i = 0; i < MI; ++i) {
             if (i >= nv) break;
             store_row_block<EPI, OB, NB, NI, false>(g, t, t.row_base + (2 * i + grp) * 32, t.n_base + wn * (BN / 4),
-                                                    nullptr, acc[i]);
+                                                    acc[i]);
         }
     }
     if (grp == 0) stage_barrier();
@@ -1301,10 +1295,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32(GroupedGemm g) {
     __shared__ __align__(16) float Bs[2][NB][kFBK][kFLD];
 
     const int total = tile_prefix<kFBM>(g.offsets, g.E, tstart);
-    // work item = tile blockIdx / ks, K part blockIdx % ks (ks = 1 unless the down-projection
-    // is split: then part p covers K steps [p nk, (p + 1) nk) and writes fp32 partial sums)
-    const int ks = (EPI == kEpiNone && g.ksplit > 1) ? g.ksplit : 1;
-    const int tile = blockIdx.x / ks, part = blockIdx.x - tile * ks;
+    const int tile = blockIdx.x;
     const int mt = tile / g.n_tiles;
     const int nt = tile - mt * g.n_tiles;
     if (mt >= total) return;
@@ -1331,10 +1322,9 @@ __global__ __launch_bounds__(kThreads) void gemm_f32(GroupedGemm g) {
     struct Regs {
         float4 a[2], b[NB][2];
     };
-    const int nk = (g.K + kFBK - 1) / kFBK / ks;  // K steps of this work item (exact when ks > 1)
-    const int kt0 = part * nk;
+    const int nk = (g.K + kFBK - 1) / kFBK;
     auto gload = [&](Regs& R, int kt) {
-        const int k = (kt0 + kt) * kFBK + lk;
+        const int k = kt * kFBK + lk;
         const bool kv = k < g.K;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -1414,16 +1404,6 @@ __global__ __launch_bounds__(kThreads) void gemm_f32(GroupedGemm g) {
     // fixed r the 32 lanes of a half-wave store 32 consecutive columns
     const int n = n0 + wn * 32 + l32;
     if (n >= g.N) return;
-    if (ks > 1) {
-        // a K part: its fp32 sums go to partial[part][row][N], the reduce kernel finishes
-        float* const dst = g.partial + static_cast<int64_t>(part) * g.rows_max * g.N;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t row = row0 + wm * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-            if (row < row_end) dst[row * g.N + n] = acc[0][r];
-        }
-        return;
-    }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         int64_t row = row0 + wm * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
@@ -1645,6 +1625,199 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
     }
 }
 
+// ------------------------------------------------------------------ few rows per expert: weights streamed into registers
+//
+// For calls whose experts have few rows (which calls: stream_rows below), where reading the
+// weights is all the time there is.  A workgroup owns NC weight rows (SwiGLU: NC / 2 of each
+// matrix) and a tile of at most 16 MR activation rows of one expert; its NW waves cut K
+// between them, so that even one expert's matrix keeps hundreds of waves loading.  A wave
+// loads fragments of v_mfma_f32_16x16x32_bf16 (fp32: of four v_mfma_f32_16x16x4_f32) straight
+// from global memory, 64 bytes of every row per K step (lane l: 16-byte chunk l / 16 of row
+// l % 16), U steps ahead of the ones it multiplies: no LDS, no barrier and no wait but the
+// loads' own until the waves add their sums, in wave order, through LDS.  Each weight is
+// loaded by one wave of one workgroup (per row tile); the activations, re-read by every
+// workgroup, come from L2.
+//
+// RAG: K is not a whole number of 64-byte steps (an up-projection on row-major weights): the
+// chunks past the end are loaded from the row's last one and replaced by zeros.
+template <typename T, int EPI, bool OB, int NC, int MR, bool RAG>
+__global__ __launch_bounds__(512, MR == 1 ? 4 : 2) void gemm_stream(GroupedGemm g) {
+    constexpr bool kBf = std::is_same<T, bf16_t>::value;
+    constexpr bool kUp = EPI != kEpiNone;
+    constexpr int ES = sizeof(T), BM = 16 * MR, NW = 8, U = NC == 64 ? 1 : 2;
+    constexpr int NB = EPI == kEpiSwiglu ? 2 : 1, BN = NC / NB, NJ = NC / 16;
+    static_assert(NJ % NB == 0, "whole 16-row blocks of each matrix");
+    constexpr bool w_blocked = kBf && !RAG;  // the packed layout
+    constexpr int kLd = NC + 4;              // LDS row stride in floats
+    __shared__ __align__(16) float red[NW][16][kLd];
+
+    RegTiles<BM> tiles;
+    tiles.build(g.offsets, g.E);
+    // contiguous runs of the tile list per XCD
+    const int total = tiles.total * g.n_tiles, per = (total + 7) >> 3;
+    const int slot = static_cast<int>(blockIdx.x >> 3);
+    const int L = static_cast<int>(blockIdx.x & 7) * per + slot;
+    if (slot >= per || L >= total) return;
+    const TileGeom t = tile_geom<BM, BN>(g, tiles, L);
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = lane & 15, chunk = lane >> 4;
+    const int64_t kbytes = static_cast<int64_t>(g.K) * ES;
+    const int nst = static_cast<int>((kbytes + 63) / 64);
+    const int s0 = static_cast<int>(static_cast<int64_t>(nst) * wave / NW);  // this wave's K steps
+    const int s1 = static_cast<int>(static_cast<int64_t>(nst) * (wave + 1) / NW);
+
+    // per-lane byte offsets of the rows from uniform bases
+    const uint32_t w_row = w_blocked ? 64u : static_cast<uint32_t>(kbytes);
+    const int64_t w_step = w_blocked ? static_cast<int64_t>(g.N) * 64 : 64;
+    const unsigned char* wbase[NB];
+    {
+        const int64_t off = t.e * g.b_estride * ES + static_cast<int64_t>(t.n0) * w_row;
+        wbase[0] = uniform_ptr(static_cast<const unsigned char*>(g.b) + off);
+        if (NB > 1) wbase[NB - 1] = uniform_ptr(static_cast<const unsigned char*>(g.b2) + off);
+    }
+    uint32_t woff[NJ / NB];
+#pragma unroll
+    for (int j = 0; j < NJ / NB; ++j)
+        woff[j] = static_cast<uint32_t>(min(16 * j + r16, g.N - 1 - t.n0)) * w_row + (RAG ? 0u : 16u * chunk);
+    // activations: row-major x, or H (bf16: K-blocked)
+    const bool a_blocked = !kUp && kBf;
+    const uint32_t a_row = a_blocked ? 64u : static_cast<uint32_t>(kbytes);
+    const int64_t a_step = a_blocked ? g.rows_max * 64 : 64;
+    const bool gathered = kUp && g.gather;
+    const unsigned char* abase = uniform_ptr(static_cast<const unsigned char*>(g.a) + (gathered ? 0 : t.row0 * a_row));
+    uint32_t aoff[MR];
+    const int valid = static_cast<int>(t.row_end - t.row0 < BM ? t.row_end - t.row0 : BM);
+    if (valid <= 0) return;
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+        const int r = min(16 * m + r16, valid - 1);
+        aoff[m] = static_cast<uint32_t>(gathered ? source_row(g, t.row0 + r) : r) * a_row + (RAG ? 0u : 16u * chunk);
+    }
+
+    struct Stage {
+        uint4 w[U][NJ], a[U][MR];
+    };
+    auto load = [&](Stage& st, int s) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t step = min(s + u, s1 - 1);
+            const int64_t at = step * 64 + 16 * chunk;
+            const uint32_t c = RAG ? static_cast<uint32_t>(at < kbytes ? at : kbytes - 16) : 0u;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const unsigned char* b = wbase[j / (NJ / NB)] + (RAG ? 0 : step * w_step);
+                st.w[u][j] = *reinterpret_cast<const uint4*>(b + (woff[j % (NJ / NB)] + c));
+            }
+#pragma unroll
+            for (int m = 0; m < MR; ++m)
+                st.a[u][m] = *reinterpret_cast<const uint4*>(abase + (RAG ? 0 : step * a_step) + (aoff[m] + c));
+            if (RAG && at >= kbytes) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) st.w[u][j] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+                for (int m = 0; m < MR; ++m) st.a[u][m] = make_uint4(0, 0, 0, 0);
+            }
+        }
+    };
+    f32x4_t acc[NJ][MR];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int m = 0; m < MR; ++m) acc[j][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](const Stage& st, int s) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s + u >= s1) break;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int m = 0; m < MR; ++m) {
+                    if constexpr (kBf) {
+                        acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(st.w[u][j]), as_bf16x8(st.a[u][m]),
+                                                                            acc[j][m], 0, 0, 0);
+                    } else {
+                        const float4 w = __builtin_bit_cast(float4, st.w[u][j]), a = __builtin_bit_cast(float4, st.a[u][m]);
+                        acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, a.x, acc[j][m], 0, 0, 0);
+                        acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, a.y, acc[j][m], 0, 0, 0);
+                        acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, a.z, acc[j][m], 0, 0, 0);
+                        acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, a.w, acc[j][m], 0, 0, 0);
+                    }
+                }
+        }
+    };
+    if (s0 < s1) {
+        Stage e, o;
+        load(e, s0);
+        for (int s = s0; s < s1; s += 2 * U) {
+            if (s + U < s1) load(o, s + U);
+            mma(e, s);
+            if (s + 2 * U < s1) load(e, s + 2 * U);
+            if (s + U < s1) mma(o, s + U);
+        }
+    }
+
+    // the waves' sums of 16 rows at a time meet in LDS (D: lane l holds row l % 16, columns
+    // 4 (l / 16) .. + 3 of each 16 x 16 block); each thread then owns pairs of columns
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+        if (m && 16 * m >= valid) break;
+        if (m) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            *reinterpret_cast<f32x4_t*>(&red[wave][r16][16 * j + 4 * chunk]) = acc[j][m];
+        __syncthreads();
+        for (int i = threadIdx.x; i < 16 * BN / 2; i += 64 * NW) {
+            const int r = i / (BN / 2), c = (i - r * (BN / 2)) * 2;
+            float2 v = *reinterpret_cast<const float2*>(&red[0][r][c]), q = v;
+            if (NB > 1) q = *reinterpret_cast<const float2*>(&red[0][r][BN + c]);
+#pragma unroll
+            for (int w = 1; w < NW; ++w) {
+                const float2 b = *reinterpret_cast<const float2*>(&red[w][r][c]);
+                v.x += b.x;
+                v.y += b.y;
+                if (NB > 1) {
+                    const float2 d = *reinterpret_cast<const float2*>(&red[w][r][BN + c]);
+                    q.x += d.x;
+                    q.y += d.y;
+                }
+            }
+            const int n = t.n0 + c;
+            if (16 * m + r >= valid || n >= g.N) continue;
+            int64_t row = t.row0 + 16 * m + r;
+            if (!kUp && g.partial) {  // whole sums in fp32, for split_combine
+                *reinterpret_cast<float2*>(g.partial + row * g.N + n) = v;
+                continue;
+            }
+            float scale = 1.f;
+            if (!kUp && g.scatter) {
+                const int64_t src = g.scatter[row];
+                row = src < 0 ? 0 : (src >= g.c_rows ? g.c_rows - 1 : src);
+                scale = g.scatter_w[row];
+            }
+            if (kBf) {
+                v.x = epilogue_fast<EPI>(v.x, q.x);
+                v.y = epilogue_fast<EPI>(v.y, q.y);
+            } else {
+                v.x = epilogue<EPI>(v.x, q.x);
+                v.y = epilogue<EPI>(v.y, q.y);
+            }
+            if (!kUp) {
+                v.x *= scale;
+                v.y *= scale;
+            }
+            if (kUp && kBf) {
+                bf16_t* const d = static_cast<bf16_t*>(g.c) + ((static_cast<int64_t>(n) >> 5) * g.rows_max + row) * 32 + (n & 31);
+                *reinterpret_cast<uint32_t*>(d) = pack_bf16x2(v.x, v.y);
+            } else if (OB) {
+                *reinterpret_cast<uint32_t*>(static_cast<bf16_t*>(g.c) + row * g.ldc + n) = pack_bf16x2(v.x, v.y);
+            } else {
+                *reinterpret_cast<float2*>(static_cast<float*>(g.c) + row * g.ldc + n) = v;
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------ split-K reduce
 //
 // out[p] = sum over s of partial[s][p] (s ascending) for the grouped rows p of the call,
@@ -1816,7 +1989,7 @@ template <int EPI, bool OB>
 hipError_t run_f32(GroupedGemm g, int64_t A_max, hipStream_t s) {
     if (g.K % kF2BK == 0) return run_f32_lds<EPI, OB>(g, A_max, s);
     g.n_tiles = static_cast<int>(ceil_div(g.N, kFBN));
-    const int64_t blocks = row_tile_bound(A_max, g.E, kFBM) * g.n_tiles * (g.ksplit > 1 ? g.ksplit : 1);
+    const int64_t blocks = row_tile_bound(A_max, g.E, kFBM) * g.n_tiles;
     if (blocks == 0) return hipSuccess;
     hipLaunchKernelGGL((gemm_f32<EPI, OB>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, s, g);
     return hipGetLastError();
@@ -1843,7 +2016,7 @@ hipError_t run_bf16_lds(GroupedGemm g, int64_t A_max, hipStream_t s) {
         hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (attr != hipSuccess) return attr;
     g.n_tiles = static_cast<int>(ceil_div(g.N, S::kBN));
-    const int64_t tiles = row_tile_bound(A_max, g.E, BM) * g.n_tiles * (g.ksplit > 1 ? g.ksplit : 1);
+    const int64_t tiles = row_tile_bound(A_max, g.E, BM) * g.n_tiles;
     if (tiles == 0) return hipSuccess;
     // persistent grid: at most per_cu workgroups per CU, a multiple of the 8 XCDs
     const int64_t blocks = round_up(std::min<int64_t>(tiles, static_cast<int64_t>(per_cu) * device_cus()), 8);
@@ -1913,16 +2086,60 @@ hipError_t run_turns(GroupedGemm g, int64_t A_max, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Which calls stream their weights (gemm_stream), from the call's row bound and its number of
+// experts: the same answer for every launch path of a call, since the waves' K parts make its
+// sums round differently.  Measured (us, up / down (+ split sum), tiled kernels against this):
+// bf16: 1 expert 16 rows (2048 x 2048) 20 / 7 + 3 against 7 / 6, 4 experts 128 rows 22 / 11 + 4
+//   against 13 / 11, 250 rows 47 / 14 + 5 against 20 / 16; 8 experts (3072 x 1536 SwiGLU) 500
+//   rows 61 / 28 + 6 against 58 / 28 + 5; 64 experts (1024 x 4096) 1000 rows 110 / 109 against
+//   110 / 101, but 2000 rows 107 / 111 against 139 / 117; 128 experts (768 x 768) 250 rows 25 / 14
+//   + 4 against 12 / 10, 1000 rows 27 / 24 against 27 / 26;
+// fp32: 8 experts (768 x 3072) 4 rows 22 / 19 + 4 against 11 / 11, 64 rows 29 / 27 + 5 against
+//   26 / 28, 128 rows 29 / 27 + 4 against 33 / 41 (its matrix rate is a sixteenth of bf16's).
+bool stream_rows(int64_t rows_max, int E, bool bf16) {
+    return bf16 ? rows_max <= 512 || rows_max <= 16 * static_cast<int64_t>(E)
+                : rows_max <= 64 || rows_max <= 8 * static_cast<int64_t>(E);
+}
+
+template <typename T, int EPI, bool OB, int NC, int MR>
+hipError_t run_stream_t(GroupedGemm g, int64_t A_max, hipStream_t s) {
+    g.n_tiles = static_cast<int>(ceil_div(g.N, EPI == kEpiSwiglu ? NC / 2 : NC));
+    const int64_t items = row_tile_bound(A_max, g.E, 16 * MR) * g.n_tiles;
+    if (items == 0) return hipSuccess;
+    const dim3 grid(static_cast<unsigned>(round_up(items, 8)));
+    if (static_cast<int64_t>(g.K) * sizeof(T) % 64 == 0)
+        hipLaunchKernelGGL((gemm_stream<T, EPI, OB, NC, MR, false>), grid, dim3(512), 0, s, g);
+    else
+        hipLaunchKernelGGL((gemm_stream<T, EPI, OB, NC, MR, true>), grid, dim3(512), 0, s, g);
+    return hipGetLastError();
+}
+
+// Weight rows per workgroup: as many of 64, 32, 16 as still give every CU two workgroups (one
+// from 48 rows on, where narrow ones re-read the activations too often: 1 expert, 64 rows 10.2 / 8.0
+// us at 32, 8.4 / 7.2 at 64; 8 experts, 4 fp32 rows 12.9 at 32, 10.9 at 16).  Row tiles of 32 where
+// experts average more than 8 rows (8 experts, 256 rows 77 / 35 -> 68 / 30 us; 64 experts, 64 rows
+// 17.0 -> 18.4 us would lose).
+template <typename T, int EPI, bool OB>
+hipError_t run_stream(GroupedGemm g, int64_t A_max, hipStream_t s) {
+    constexpr int kMin = EPI == kEpiSwiglu ? 32 : 16;
+    const int64_t tiles = std::min<int64_t>(A_max, g.E + A_max / 16);
+    const int64_t want = (A_max < 48 ? 2 : 1) * static_cast<int64_t>(device_cus());
+    int nc = 64;
+    while (nc > kMin && tiles * ceil_div(g.N, EPI == kEpiSwiglu ? nc / 2 : nc) < want) nc /= 2;
+    if constexpr (kMin == 16) {
+        if (nc == 16) return run_stream_t<T, EPI, OB, 16, 1>(g, A_max, s);
+    }
+    if (nc == 32) return run_stream_t<T, EPI, OB, 32, 1>(g, A_max, s);
+    if constexpr (std::is_same<T, bf16_t>::value) {
+        if (A_max > 8 * static_cast<int64_t>(g.E)) return run_stream_t<T, EPI, OB, 64, 2>(g, A_max, s);
+    }
+    return run_stream_t<T, EPI, OB, 64, 1>(g, A_max, s);
+}
+
 template <int EPI, bool OB>
 hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
     constexpr bool kUp = EPI != kEpiNone;
     if constexpr (kUp) {
-        // Decode-sized calls (at most 128 rows: a few row tiles) take 64 x 128 tiles: twice
-        // the workgroups of 256-column tiles streaming the weights, and half the activation
-        // rows per stage of 128-row tiles, most of which are empty at this size (measured on
-        // a 64-token top-2 step: about 10 us less than 128 x 256, 1.6 us less than 128 x 128;
-        // no gain from 256 rows up, where the tiles already cover the CUs).
-        if (A_max <= 128 && g.K % 32 == 0) return run_bf16_lds<64, 128, 32, 3, EPI, OB>(g, A_max, s);
         if (turns_up(g, A_max, static_cast<int>(ceil_div(g.N, EPI == kEpiSwiglu ? 128 : 256))))
             return run_turns<EPI, OB>(g, A_max, s);
         // activation rows in 128-byte pieces when K allows it (see gemm_up_pairs)
@@ -1933,8 +2150,6 @@ hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
         return run_bf16<EPI, OB, true>(g, A_max, s);
     } else {
         if (g.K % 32 != 0) return hipErrorInvalidValue;  // not reachable through the C ABI (fp % 128 == 0)
-        if (g.ksplit > 1 && A_max <= 128) return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
-        if (g.ksplit > 1) return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);
         if (turns_down(g, A_max)) return run_turns<EPI, OB>(g, A_max, s);
         if (g.N >= 384 && row_tile_bound(A_max, g.E, 128) * ceil_div(g.N, 384) <= device_cus())
             return run_bf16_lds<128, 384, 32, 3, EPI, OB, 4>(g, A_max, s);
@@ -1943,7 +2158,8 @@ hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
 }
 
 template <int EPI>
-hipError_t gemm1(bool bf16, GroupedGemm g, int64_t A_max, hipStream_t s) {
+hipError_t gemm1(bool bf16, bool stream, GroupedGemm g, int64_t A_max, hipStream_t s) {
+    if (stream) return bf16 ? run_stream<bf16_t, EPI, true>(g, A_max, s) : run_stream<float, EPI, false>(g, A_max, s);
     return bf16 ? run_bf16_best<EPI, true>(g, A_max, s) : run_f32<EPI, false>(g, A_max, s);
 }
 
@@ -1972,23 +2188,12 @@ hipError_t launch_split_reduce_t(const float* partial, int64_t rows_max, int h, 
     return hipGetLastError();
 }
 
-// S = the down-projection's K parts: 2, 4 or 8 (down_ksplit)
-hipError_t launch_split_reduce(bool ob, int S, const float* partial, int64_t rows_max, int h, int64_t grid_rows,
+// four parts: the fp32 down-projection's (down_ksplit)
+hipError_t launch_split_reduce(bool ob, const float* partial, int64_t rows_max, int h, int64_t grid_rows,
                                const int32_t* offsets, int E, void* out, const int32_t* scatter,
                                const float* scatter_w, int64_t c_rows, hipStream_t s) {
-#define MOE_SPLIT_REDUCE(OBV, SV) \
-    return launch_split_reduce_t<OBV, SV>(partial, rows_max, h, grid_rows, offsets, E, out, scatter, scatter_w, c_rows, s)
-    if (ob) {
-        if (S == 2) MOE_SPLIT_REDUCE(true, 2);
-        if (S == 4) MOE_SPLIT_REDUCE(true, 4);
-        if (S == 8) MOE_SPLIT_REDUCE(true, 8);
-    } else {
-        if (S == 2) MOE_SPLIT_REDUCE(false, 2);
-        if (S == 4) MOE_SPLIT_REDUCE(false, 4);
-        if (S == 8) MOE_SPLIT_REDUCE(false, 8);
-    }
-#undef MOE_SPLIT_REDUCE
-    return hipErrorInvalidValue;
+    return ob ? launch_split_reduce_t<true, 4>(partial, rows_max, h, grid_rows, offsets, E, out, scatter, scatter_w, c_rows, s)
+              : launch_split_reduce_t<false, 4>(partial, rows_max, h, grid_rows, offsets, E, out, scatter, scatter_w, c_rows, s);
 }
 
 template <bool YB, bool OB, int S>
@@ -2003,9 +2208,8 @@ hipError_t launch_split_combine(bool yb, int S, const float* partial, int64_t ro
                                 hipStream_t s) {
 #define MOE_SPLIT_COMBINE(YBV, OBV)                                                              \
     do {                                                                                       \
-        if (S == 2) return launch_split_combine_t<YBV, OBV, 2>(partial, rows_max, h, c, s);   \
+        if (S == 1) return launch_split_combine_t<YBV, OBV, 1>(partial, rows_max, h, c, s);   \
         if (S == 4) return launch_split_combine_t<YBV, OBV, 4>(partial, rows_max, h, c, s);   \
-        if (S == 8) return launch_split_combine_t<YBV, OBV, 8>(partial, rows_max, h, c, s);   \
     } while (0)
     if (yb && c.y_bf16) MOE_SPLIT_COMBINE(true, true);
     else if (yb) MOE_SPLIT_COMBINE(true, false);
@@ -2018,8 +2222,11 @@ hipError_t launch_split_combine(bool yb, int S, const float* partial, int64_t ro
 hipError_t ffn_pair(const void* x_perm, const int32_t* offsets, int64_t grid_rows, int64_t rows_max, int E,
                     int h, int64_t fp, int act, bool bf16, const void* w1t, const void* w3t, const void* w2t,
                     void* y_perm, bool y_bf16, void* hbuf, hipStream_t s, const int32_t* gather = nullptr,
-                    int64_t a_rows = 0, const float* scatter_w = nullptr, const CombineArgs* comb = nullptr) {
+                    int64_t a_rows = 0, const float* scatter_w = nullptr, const CombineArgs* comb = nullptr,
+                    int call_E = 0) {
     if (grid_rows == 0) return hipSuccess;
+    // call_E: the call's experts where this launch covers one of them
+    const bool stream = stream_rows(rows_max, call_E ? call_E : E, bf16);
     GroupedGemm g1{};
     g1.a = x_perm;
     g1.gather = gather;
@@ -2035,9 +2242,9 @@ hipError_t ffn_pair(const void* x_perm, const int32_t* offsets, int64_t grid_row
     g1.b_estride = fp * h;
     g1.rows_max = rows_max;
     hipError_t err;
-    if (act == MOE_ACT_SWIGLU) err = gemm1<kEpiSwiglu>(bf16, g1, grid_rows, s);
-    else if (act == MOE_ACT_GELU_TANH) err = gemm1<kEpiGeluTanh>(bf16, g1, grid_rows, s);
-    else err = gemm1<kEpiGelu>(bf16, g1, grid_rows, s);
+    if (act == MOE_ACT_SWIGLU) err = gemm1<kEpiSwiglu>(bf16, stream, g1, grid_rows, s);
+    else if (act == MOE_ACT_GELU_TANH) err = gemm1<kEpiGeluTanh>(bf16, stream, g1, grid_rows, s);
+    else err = gemm1<kEpiGelu>(bf16, stream, g1, grid_rows, s);
     if (err != hipSuccess) return err;
 
     GroupedGemm g2{};
@@ -2057,27 +2264,31 @@ hipError_t ffn_pair(const void* x_perm, const int32_t* offsets, int64_t grid_row
         g2.scatter_w = scatter_w;
         g2.c_rows = a_rows;
     }
+    // fp32 sums after H in the workspace: ksplit x rows_max x h
+    float* const partial = reinterpret_cast<float*>(static_cast<unsigned char*>(hbuf) +
+                                                    round_up(rows_max * fp * (bf16 ? 2 : 4), 256));
+    if (stream) {
+        // whole sums: straight into y_perm, or for split_combine as one part
+        if (comb) g2.partial = partial;
+        if (bf16) err = y_bf16 ? run_stream<bf16_t, kEpiNone, true>(g2, grid_rows, s) : run_stream<bf16_t, kEpiNone, false>(g2, grid_rows, s);
+        else err = y_bf16 ? run_stream<float, kEpiNone, true>(g2, grid_rows, s) : run_stream<float, kEpiNone, false>(g2, grid_rows, s);
+        if (err != hipSuccess || !comb || comb->T == 0) return err;
+        return launch_split_combine(y_bf16, 1, partial, rows_max, h, *comb, s);
+    }
+    if (bf16) return y_bf16 ? run_bf16_best<kEpiNone, true>(g2, grid_rows, s) : run_bf16_best<kEpiNone, false>(g2, grid_rows, s);
     // the split is chosen from rows_max (the call's row bound), so a per-expert launch of
     // this call splits like the grouped one
-    g2.ksplit = down_ksplit(rows_max, fp, bf16);
-    if (g2.ksplit <= 1) {
-        if (!bf16) return y_bf16 ? run_f32<kEpiNone, true>(g2, grid_rows, s) : run_f32<kEpiNone, false>(g2, grid_rows, s);
-        return y_bf16 ? run_bf16_best<kEpiNone, true>(g2, grid_rows, s) : run_bf16_best<kEpiNone, false>(g2, grid_rows, s);
-    }
-    // partial tiles after H in the workspace: ksplit x rows_max x h fp32
-    g2.partial = reinterpret_cast<float*>(static_cast<unsigned char*>(hbuf) +
-                                          round_up(rows_max * fp * (bf16 ? 2 : 4), 256));
-    if (bf16)
-        err = y_bf16 ? run_bf16_best<kEpiNone, true>(g2, grid_rows, s) : run_bf16_best<kEpiNone, false>(g2, grid_rows, s);
-    else
-        err = run_f32<kEpiNone, false>(g2, grid_rows, s);  // partial tiles only
+    g2.ksplit = down_ksplit(rows_max, fp, false);
+    if (g2.ksplit <= 1) return y_bf16 ? run_f32<kEpiNone, true>(g2, grid_rows, s) : run_f32<kEpiNone, false>(g2, grid_rows, s);
+    g2.partial = partial;
+    err = run_f32<kEpiNone, false>(g2, grid_rows, s);  // partial tiles only
     if (err != hipSuccess) return err;
     if (comb) {
         if (comb->T == 0) return hipSuccess;
-        return launch_split_combine(y_bf16, g2.ksplit, g2.partial, rows_max, h, *comb, s);
+        return launch_split_combine(y_bf16, g2.ksplit, partial, rows_max, h, *comb, s);
     }
-    return launch_split_reduce(y_bf16, g2.ksplit, g2.partial, rows_max, h, grid_rows, offsets, E, y_perm,
-                               g2.scatter, g2.scatter_w, g2.c_rows, s);
+    return launch_split_reduce(y_bf16, partial, rows_max, h, grid_rows, offsets, E, y_perm, g2.scatter, g2.scatter_w,
+                               g2.c_rows, s);
 }
 
 }  // namespace
@@ -2193,7 +2404,7 @@ hipError_t launch_ffn_per_expert(const void* x_perm, const int32_t* offsets, con
         const unsigned char* b3 = w3t ? static_cast<const unsigned char*>(w3t) + e * mat : nullptr;
         const unsigned char* b2 = static_cast<const unsigned char*>(w2t) + e * mat;
         const hipError_t err = ffn_pair(x_perm, offsets + e, count, A_max, 1, h, fp, act, bf16, b1, b3, b2, y_perm,
-                                        y_bf16, hbuf, s);
+                                        y_bf16, hbuf, s, nullptr, 0, nullptr, nullptr, E);
         if (err != hipSuccess) return err;
     }
     return hipSuccess;

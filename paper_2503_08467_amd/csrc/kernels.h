@@ -11,13 +11,13 @@ namespace moe {
 constexpr int kInnerAlign = 128;  // packed inner width is a multiple of this
 constexpr int kDispatchChunk = 1024;  // assignments per dispatch workgroup
 
-// K parts of the down-projection.  A call with few rows has few row tiles, each with a long
-// K loop, and leaves most CUs idle; splitting K spreads the weight reads over more workgroups
-// (fp32 partial tiles, summed in a fixed order afterwards).  A function of the call's sizes
-// only (the row bound, not the routing), so every launch path of one call shape rounds the
-// same way.  fp is the packed inner width (a multiple of kInnerAlign).
-//   bf16: up to 8 parts for at most 512 rows (measured: no gain from 1024 rows up);
-//   fp32: 4 parts for at most 1024 rows (its K loop is four times as slow as bf16's).
+// K parts of the down-projection that the workspace has room for; more than one marks the
+// decode-sized calls whose fp32 sums go to the combine through the workspace.  A function of
+// the call's sizes only (the row bound, not the routing), so every launch path of one call
+// rounds the same way.  fp is the packed inner width (a multiple of kInnerAlign).
+//   bf16: at most 512 rows; these stream their weights and hand over whole sums (one part);
+//   fp32: 4 parts for at most 1024 rows, so that few row tiles with a long K loop each spread
+//   their weight reads over more workgroups (gemm_f32_lds; fewer rows stream, one part).
 inline int down_ksplit(int64_t A_max, int64_t fp, bool bf16) {
     const int64_t nk = fp / 32;  // K steps of 32
     if (!bf16) return (A_max <= 1024 && nk % 4 == 0 && nk / 4 >= 8) ? 4 : 1;
@@ -79,8 +79,8 @@ hipError_t launch_ffn_gather(const void* x, int64_t T, const int32_t* row_src, c
                              int E, int h, int64_t fp, int act, bool bf16, const void* w1t, const void* w3t,
                              const void* w2t, void* y_perm, bool y_bf16, void* hbuf, hipStream_t s);
 
-// launch_ffn_gather followed by launch_combine; when the second product's K is split, its
-// parts' sum and the combine run as one kernel and y_perm is not written (*y_perm_written).
+// launch_ffn_gather followed by launch_combine; where down_ksplit > 1 the second product's
+// fp32 sums go straight to the combine and y_perm is not written (*y_perm_written).
 hipError_t launch_ffn_gather_combine(const void* x, int64_t T, const int32_t* row_src, const int32_t* offsets, int k,
                                      int E, int h, int64_t fp, int act, bool bf16, const void* w1t, const void* w3t,
                                      const void* w2t, void* y_perm, bool y_bf16, const int32_t* pos_of,

@@ -257,7 +257,7 @@ def expert_ffn_shard_gather_combine(x: torch.Tensor, row_src: torch.Tensor, offs
                                     out: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None,
                                     stream=None):
     """Steps 4 and 5 for any k: the gathered expert step and the weighted combine in one call
-    (one launch for both when the second product's K is split).  Returns (y, y_perm or None
+    (decode-sized calls hand fp32 sums from one to the other).  Returns (y, y_perm or None
     when y_perm was not written)."""
     _dev(x, "x"), _dev(row_src, "row_src"), _dev(offsets, "offsets"), _dev(pos_of, "pos_of"), _dev(topk_w, "topk_w")
     if x.dtype != packed.dtype:
@@ -409,8 +409,7 @@ class MoEShardLayer:
             y = expert_ffn_shard_top1(x, d.row_src, w.view(-1), d.offsets, self.packed, out=self.y[:T], ws=self.fws)
         else:
             if d.x_perm is None:
-                # Steps 4 and 5 in one call (one launch for the split sum and the combine when
-                # the second product's K is split; y_perm is then not written)
+                # Steps 4 and 5 in one call (decode-sized calls do not write y_perm)
                 y, y_perm = expert_ffn_shard_gather_combine(x, d.row_src, d.offsets, d.pos_of, w, self.packed,
                                                             y_perm=self.y_perm[:T * k], out=self.y[:T], ws=self.fws)
             else:

@@ -295,6 +295,45 @@ def test_ffn_parity_on_random_shapes(i, counts, h, f, act, dtype):
         assert rowwise(got, ref) <= TOL[dtype], (rowwise(got, ref), normwise(got, ref))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("act", ["gelu", "gelu_tanh", "swiglu"])
+@pytest.mark.parametrize("counts,h,f", [
+    ([1], 8, 1),                         # one 16-byte chunk of K: most waves have none
+    ([16, 0, 17, 1, 15], 200, 129),      # row-tile edges; K ends inside a step for both types
+    ([0, 31, 33], 1032, 40),             # N past a 64-row block by 8; ragged K in bf16 only from 40
+    ([5] * 40, 136, 64),                 # many experts, narrow shards
+    ([64, 0], 1544, 300),                # 32-row tiles for bf16 (more than 8 rows per expert)
+    ([300, 212], 64, 1000),              # 512 rows: the most that always stream in bf16
+    ([9] * 72, 32, 96),                  # 648 rows: streamed for their number of experts (bf16)
+])
+def test_streamed_weights(dtype, act, counts, h, f):
+    """Calls with few rows per expert: the expert step through every entry point (x_perm, fp32
+    partials, gathered rows with the combine folded in, top-1) against the oracle."""
+    rng = np.random.default_rng(sum(counts) + h + 7 * f)
+    x, w1, w3, w2, offsets = _ffn_case(rng, counts, h, f, act, dtype)
+    dt, A = tdt(dtype), len(x)
+    packed = moe.pack_weights(to_dev(w1, dt), to_dev(w2, dt), to_dev(w3, dt), act=act)
+    xd, od = to_dev(x, dt), to_dev(offsets, torch.int32)
+    ref = oracle.expert_ffn(x, offsets, w1, w3, w2, act)
+    tol = TOL[dtype]
+    y32 = moe.expert_ffn_shard(xd, od, packed, out_dtype=torch.float32)
+    y = moe.expert_ffn_shard(xd, od, packed)
+    each = moe.expert_ffn_shard_per_expert(xd, od, packed)
+    # a token order that is not the grouped one: token t's row is at position inv[t]
+    perm = rng.permutation(A).astype(np.int32)
+    inv = np.argsort(perm).astype(np.int32)
+    wt = rng.uniform(0.1, 1.0, A).astype(np.float32)
+    xt, src, wd = to_dev(x[inv], dt), to_dev(perm, torch.int32), to_dev(wt, torch.float32)
+    top1 = moe.expert_ffn_shard_top1(xt, src, wd, od, packed)
+    one, _ = moe.expert_ffn_shard_gather_combine(xt, src, od, to_dev(inv[:, None], torch.int32), wd[:, None].contiguous(),
+                                                 packed)
+    torch.cuda.synchronize()
+    assert torch.equal(y, each) and torch.equal(y, y32.to(dt))
+    assert rowwise(np_of(y32), ref) <= tol and rowwise(np_of(y), ref) <= tol
+    for got in (top1, one):
+        assert rowwise(np_of(got), wt[:, None] * ref[inv]) <= tol
+
+
 @pytest.mark.parametrize("act", ["gelu", "gelu_tanh", "swiglu"])
 @pytest.mark.parametrize("counts,h,f", [
     ([600], 72, 1536),                # down-projection on 256 x 256 tiles: N below one tile
