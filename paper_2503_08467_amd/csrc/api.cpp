@@ -108,7 +108,7 @@ moe_status moe_route_dispatch(const void* x, moe_dtype xdt, int64_t T, int64_t h
     if (ws_bytes < moe_dispatch_workspace_size(T, k, E)) return MOE_ERR_WORKSPACE;
     const bool bf16 = xdt == MOE_BF16;
     if (moe::route_dispatch_fusable(bf16, T, static_cast<int>(h), E, k))
-        return from_hip(moe::launch_route_dispatch(x, T, static_cast<int>(h), w_gate, E, k, sel_bias, bias_row_stride,
+        return from_hip(moe::launch_route_dispatch(x, bf16, T, static_cast<int>(h), w_gate, E, k, sel_bias, bias_row_stride,
                                                    renorm, topk_idx, topk_w,
                                                    moe::RouteDispatchOut{counts, offsets, row_src, pos_of}, stream));
     if (any) {

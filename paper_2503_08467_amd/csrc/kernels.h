@@ -55,11 +55,11 @@ struct RouteDispatchOut {
 };
 
 // Whether one routing workgroup covers the whole batch, so that it can also group the
-// assignments: bf16, h % 64 == 0, 32 < E <= 256, 1 <= T <= 64, k <= 8.
+// assignments: k <= 8 and T at most 64 (16 or 32 for the larger E of some types).
 bool route_dispatch_fusable(bool bf16, int64_t T, int h, int E, int k);
 
 // Steps 1 and 2 in one launch (only when route_dispatch_fusable).
-hipError_t launch_route_dispatch(const void* x, int64_t T, int h, const void* wg, int E, int k, const float* bias,
+hipError_t launch_route_dispatch(const void* x, bool bf16, int64_t T, int h, const void* wg, int E, int k, const float* bias,
                                  int64_t bias_stride, int renorm, int32_t* idx, float* w, RouteDispatchOut out,
                                  hipStream_t s);
 

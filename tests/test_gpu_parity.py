@@ -112,6 +112,31 @@ def test_route_dispatch_matches_two_calls(T, h, E, k, bias_kind):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,h,E,k", [(1, 8, 1, 1), (16, 40, 16, 3), (17, 24, 17, 2), (33, 1000, 32, 8), (64, 64, 8, 2),
+                                     (65, 64, 8, 2), (16, 72, 64, 2), (17, 72, 60, 2), (32, 136, 128, 4),
+                                     (33, 136, 100, 4), (16, 520, 256, 8), (17, 264, 200, 1)])
+def test_route_and_grouping_in_one_call(dtype, T, h, E, k):
+    """Around every limit of the one-launch form (16, 32 or 64 tokens by type and experts) and
+    with K ending inside a 64-byte step: the picks against the oracle, and every output of the
+    one call bit for bit that of the two."""
+    rng = np.random.default_rng(T * 31 + h + E)
+    x = rng.standard_normal((T, h)).astype(np.float32)
+    wg = (rng.standard_normal((E, h)) * 0.05).astype(np.float32)
+    if dtype == "bf16":
+        x, wg = synth.round_to_bf16(x), synth.round_to_bf16(wg)
+    bias = rng.standard_normal((T, E)).astype(np.float32)
+    _check_route(x, wg, bias, k, k > 1, dtype, False)
+    xd, wd, bd = to_dev(x, tdt(dtype)), to_dev(wg, tdt(dtype)), to_dev(bias, torch.float32)
+    i1, w1 = moe.route(xd, wd, k, bd, k > 1)
+    d1 = moe.dispatch(i1, xd, E, x_perm=False)
+    i2, w2, d2 = moe.route_dispatch(xd, wd, k, bd, k > 1)
+    torch.cuda.synchronize()
+    assert torch.equal(i1, i2) and torch.equal(w1, w2)
+    for key in ("counts", "offsets", "pos_of", "row_src"):
+        assert torch.equal(getattr(d1, key), getattr(d2, key)), key
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_route_exact_ties_go_to_lower_expert(dtype):
     rng = np.random.default_rng(5)
     T, h, E = 200, 64, 40
