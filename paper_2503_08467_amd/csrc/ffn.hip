@@ -2095,10 +2095,15 @@ hipError_t run_turns(GroupedGemm g, int64_t A_max, hipStream_t s) {
 //   110 / 101, but 2000 rows 107 / 111 against 139 / 117; 128 experts (768 x 768) 250 rows 25 / 14
 //   + 4 against 12 / 10, 1000 rows 27 / 24 against 27 / 26;
 // fp32: 8 experts (768 x 3072) 4 rows 22 / 19 + 4 against 11 / 11, 64 rows 29 / 27 + 5 against
-//   26 / 28, 128 rows 29 / 27 + 4 against 33 / 41 (its matrix rate is a sixteenth of bf16's).
-bool stream_rows(int64_t rows_max, int E, bool bf16) {
-    return bf16 ? rows_max <= 512 || rows_max <= 16 * static_cast<int64_t>(E)
-                : rows_max <= 64 || rows_max <= 8 * static_cast<int64_t>(E);
+//   26 / 28, 128 rows 29 / 27 + 4 against 33 / 41 (its matrix rate is a sixteenth of bf16's);
+//   only where the tiled kernel's up-projection has at most one 128-column tile per CU: with
+//   more, its 128-byte pieces of a row stream the weights faster (layers of 24 experts 3456 x 488
+//   167 -> 136, 64 experts 2624 x 168 203 -> 173, but 96 experts 832 x 1216 112 -> 136, 64 experts
+//   640 x 2564 209 -> 253).
+bool stream_rows(int64_t rows_max, int E, int64_t fp, bool bf16) {
+    if (bf16) return rows_max <= 512 || rows_max <= 16 * static_cast<int64_t>(E);
+    return (rows_max <= 64 || rows_max <= 8 * static_cast<int64_t>(E)) &&
+           std::min<int64_t>(rows_max, E) * (fp / 128) <= device_cus();
 }
 
 template <typename T, int EPI, bool OB, int NC, int MR>
@@ -2226,7 +2231,7 @@ hipError_t ffn_pair(const void* x_perm, const int32_t* offsets, int64_t grid_row
                     int call_E = 0) {
     if (grid_rows == 0) return hipSuccess;
     // call_E: the call's experts where this launch covers one of them
-    const bool stream = stream_rows(rows_max, call_E ? call_E : E, bf16);
+    const bool stream = stream_rows(rows_max, call_E ? call_E : E, fp, bf16);
     GroupedGemm g1{};
     g1.a = x_perm;
     g1.gather = gather;
