@@ -29,7 +29,7 @@ def _torch_dtype(code: int) -> torch.dtype:
 
 
 def _dev(t: torch.Tensor, name: str) -> torch.Tensor:
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor (no CPU path exists)")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
@@ -41,26 +41,37 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(t: torch.Tensor, stream) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream(t.device)
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # the raw handle of torch.cuda.current_stream(t.device), without building a Stream object
+    # (0.2 us against 4)
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
-def route(x: torch.Tensor, w_gate: torch.Tensor, k: int, sel_bias: Optional[torch.Tensor] = None,
-          renorm: bool = False, out=None, stream=None):
-    """Step 1: returns (topk_idx [T,k] int32, topk_w [T,k] float32)."""
+def _bias_stride(x: torch.Tensor, w_gate: torch.Tensor, sel_bias: Optional[torch.Tensor]) -> int:
+    """Checks the routing inputs; returns the row stride of the selection bias."""
     _dev(x, "x"), _dev(w_gate, "w_gate")
     T, h = x.shape
     E = w_gate.shape[0]
     if w_gate.shape[1] != h or w_gate.dtype != x.dtype:
         raise ValueError("w_gate must be [E, h] with the dtype of x")
-    stride = 0
-    if sel_bias is not None:
-        _dev(sel_bias, "sel_bias")
-        if sel_bias.dtype != torch.float32:
-            raise TypeError("sel_bias must be float32")
-        stride = 0 if sel_bias.dim() == 1 else E
-        if sel_bias.numel() != (E if stride == 0 else T * E):
-            raise ValueError("sel_bias must be [E] or [T, E]")
+    if sel_bias is None:
+        return 0
+    _dev(sel_bias, "sel_bias")
+    if sel_bias.dtype != torch.float32:
+        raise TypeError("sel_bias must be float32")
+    stride = 0 if sel_bias.dim() == 1 else E
+    if sel_bias.numel() != (E if stride == 0 else T * E):
+        raise ValueError("sel_bias must be [E] or [T, E]")
+    return stride
+
+
+def route(x: torch.Tensor, w_gate: torch.Tensor, k: int, sel_bias: Optional[torch.Tensor] = None,
+          renorm: bool = False, out=None, stream=None):
+    """Step 1: returns (topk_idx [T,k] int32, topk_w [T,k] float32)."""
+    stride = _bias_stride(x, w_gate, sel_bias)
+    T, h = x.shape
+    E = w_gate.shape[0]
     if out is None:
         idx = torch.empty((T, k), dtype=torch.int32, device=x.device)
         w = torch.empty((T, k), dtype=torch.float32, device=x.device)
@@ -117,19 +128,9 @@ def route_dispatch(x: torch.Tensor, w_gate: torch.Tensor, k: int, sel_bias: Opti
                    stream=None):
     """Steps 1 and 2 in one call (one launch for decode-sized batches); the dispatch writes
     indices only (no x_perm).  Returns (topk_idx, topk_w, Dispatch)."""
-    _dev(x, "x"), _dev(w_gate, "w_gate")
+    stride = _bias_stride(x, w_gate, sel_bias)
     T, h = x.shape
     E = w_gate.shape[0]
-    if w_gate.shape[1] != h or w_gate.dtype != x.dtype:
-        raise ValueError("w_gate must be [E, h] with the dtype of x")
-    stride = 0
-    if sel_bias is not None:
-        _dev(sel_bias, "sel_bias")
-        if sel_bias.dtype != torch.float32:
-            raise TypeError("sel_bias must be float32")
-        stride = 0 if sel_bias.dim() == 1 else E
-        if sel_bias.numel() != (E if stride == 0 else T * E):
-            raise ValueError("sel_bias must be [E] or [T, E]")
     if out is None:
         idx = torch.empty((T, k), dtype=torch.int32, device=x.device)
         w = torch.empty((T, k), dtype=torch.float32, device=x.device)
@@ -375,6 +376,7 @@ class MoEShardLayer:
         # fold the dispatch row gather into the expert step (no x_perm buffer)
         self.fused_gather = fused_gather
         self._cap = 0
+        self._last = None
         if max_tokens:
             self._alloc(max_tokens)
 
@@ -393,30 +395,60 @@ class MoEShardLayer:
         T = x.shape[0]
         if T > self._cap:
             self._alloc(T)
+        if self.disp.x_perm is None:
+            return self._forward_fused(x, sel_bias, T)
         k = self.k
         idx, w = self.idx[:T], self.w[:T]
         d = Dispatch(self.disp.counts, self.disp.offsets, self.disp.row_src[:T * k], self.disp.pos_of[:T],
-                     None if self.disp.x_perm is None else self.disp.x_perm[:T * k])
-        if d.x_perm is None:
-            # Steps 1 and 2 in one call (one launch when a single workgroup routes the batch)
-            route_dispatch(x, self.w_gate, k, sel_bias, self.renorm, out=(idx, w), disp=d, ws=self.dws)
-        else:
-            route(x, self.w_gate, k, sel_bias, self.renorm, out=(idx, w))
-            dispatch(idx, x, self.E, out=d, ws=self.dws)
-        if d.x_perm is None and k == 1:
-            # top-1: the expert step writes the weighted rows straight into y
-            y_perm = None
-            y = expert_ffn_shard_top1(x, d.row_src, w.view(-1), d.offsets, self.packed, out=self.y[:T], ws=self.fws)
-        else:
-            if d.x_perm is None:
-                # Steps 4 and 5 in one call (decode-sized calls do not write y_perm)
-                y, y_perm = expert_ffn_shard_gather_combine(x, d.row_src, d.offsets, d.pos_of, w, self.packed,
-                                                            y_perm=self.y_perm[:T * k], out=self.y[:T], ws=self.fws)
-            else:
-                y_perm = expert_ffn_shard(d.x_perm, d.offsets, self.packed, A_max=T * k, out=self.y_perm[:T * k],
-                                          ws=self.fws)
-                y = combine(y_perm, d.pos_of, w, out=self.y[:T])
-        self.last = dict(idx=idx, w=w, dispatch=d, y_perm=y_perm)
+                     self.disp.x_perm[:T * k])
+        route(x, self.w_gate, k, sel_bias, self.renorm, out=(idx, w))
+        dispatch(idx, x, self.E, out=d, ws=self.dws)
+        y_perm = expert_ffn_shard(d.x_perm, d.offsets, self.packed, A_max=T * k, out=self.y_perm[:T * k], ws=self.fws)
+        y = combine(y_perm, d.pos_of, w, out=self.y[:T])
+        self._last = dict(idx=idx, w=w, dispatch=d, y_perm=y_perm)
         return y
+
+    def _forward_fused(self, x: torch.Tensor, sel_bias: Optional[torch.Tensor], T: int) -> torch.Tensor:
+        """route_dispatch, then expert_ffn_shard_top1 (k = 1: the expert step writes the weighted
+        rows straight into y) or expert_ffn_shard_gather_combine, on the layer's own buffers.  The
+        two library calls are made from here: through those functions, with a view made of
+        every buffer, a decode step spent longer in Python than on the GPU (one token: 28 us of
+        host time a step, 17 like this)."""
+        w_gate, packed, d, k = self.w_gate, self.packed, self.disp, self.k
+        stride = _bias_stride(x, w_gate, sel_bias)
+        if x.dtype != packed.dtype:
+            raise TypeError("x must have the packed weights' dtype")
+        stream = _stream(x, None)
+        h, dt, xp = x.shape[1], _DT[x.dtype], x.data_ptr()
+        wp, offp, srcp, posp = self.w.data_ptr(), d.offsets.data_ptr(), d.row_src.data_ptr(), d.pos_of.data_ptr()
+        _lib.call("moe_route_dispatch", xp, dt, T, h, w_gate.data_ptr(), w_gate.shape[0], k, _ptr(sel_bias), stride,
+                  int(bool(self.renorm)), self.idx.data_ptr(), wp, d.counts.data_ptr(), offp, srcp, posp,
+                  self.dws.data_ptr(), self.dws.numel(), stream)
+        act, pp = _lib.ACTS[packed.act], packed.buf.data_ptr()
+        yp, ydt = self.y.data_ptr(), _DT[self.y.dtype]
+        fwp, fwn = self.fws.data_ptr(), self.fws.numel()
+        if k == 1:
+            written = 0
+            _lib.call("moe_expert_ffn_shard_top1", xp, T, srcp, wp, offp, packed.E, packed.h, packed.f, act, dt, pp, yp,
+                      ydt, fwp, fwn, stream)
+        else:
+            flag = ctypes.c_int32(0)
+            _lib.call("moe_expert_ffn_shard_gather_combine", xp, T, srcp, offp, posp, wp, k, packed.E, packed.h,
+                      packed.f, act, dt, pp, self.y_perm.data_ptr(), _DT[self.y_perm.dtype], yp, ydt,
+                      ctypes.addressof(flag), fwp, fwn, stream)
+            written = flag.value
+        self._last = (T, k, self.idx, self.w, d, self.y_perm if written else None)
+        return self.y[:T]
+
+    @property
+    def last(self) -> dict:
+        """Routing, grouping and (where it was written) y_perm of the last forward()."""
+        if self._last is None:
+            raise AttributeError("no forward() yet")
+        if isinstance(self._last, tuple):
+            T, k, idx, w, d, y_perm = self._last
+            self._last = dict(idx=idx[:T], w=w[:T], y_perm=None if y_perm is None else y_perm[:T * k],
+                              dispatch=Dispatch(d.counts, d.offsets, d.row_src[:T * k], d.pos_of[:T], None))
+        return self._last
 
     __call__ = forward
