@@ -563,6 +563,34 @@ def test_top1_step_writes_weighted_rows(dtype, out_dtype, act, T, E, h, f):
     assert np.all(y[~valid] == 7.0)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("h,F,col0,f", [
+    (72, 264, 8, 200),     # 16-byte source runs, the last one past the slice
+    (64, 264, 12, 128),    # runs start off 16 bytes in bf16 only
+    (200, 131, 3, 67),     # odd row length and offset: single elements
+    (1032, 640, 128, 512), # whole tiles and a remainder of 8
+])
+def test_packed_slice_matches_a_copy_of_it(dtype, h, F, col0, f):
+    """Packing columns [col0, col0 + f) of wide weights gives the bytes that packing a contiguous
+    copy of the slice gives, element loads or 16-byte ones."""
+    dt, g = tdt(dtype), torch.Generator(device="cuda").manual_seed(h + F)
+    w1, w2, w3 = (torch.randn(shape, generator=g, device="cuda").to(dt) for shape in ((3, h, F), (3, F, h), (3, h, F)))
+    a = moe.pack_weights(w1, w2, w3, col0=col0, f=f, act="swiglu")
+    cut = slice(col0, col0 + f)
+    b = moe.pack_weights(w1[:, :, cut].contiguous(), w2[:, cut].contiguous(), w3[:, :, cut].contiguous(), act="swiglu")
+    torch.cuda.synchronize()
+    n = 3 * h * moe.padded_inner_width(f)  # the first matrix; the others start on 256 bytes
+    va, vb = (p.buf[: n * dt.itemsize].view(dt) for p in (a, b))
+    assert torch.equal(va, vb)
+    # every source element is there (the rest is padding)
+    kept = va.float()
+    assert float(kept.sum(dtype=torch.float64)) == pytest.approx(float(w1[:, :, cut].double().sum()), abs=1e-6 * n)
+    assert int((kept != 0).sum()) == int((w1[:, :, cut] != 0).sum())
+    x = torch.randn((40, h), generator=g, device="cuda").to(dt)
+    off = torch.tensor([0, 10, 10, 40], dtype=torch.int32, device="cuda")
+    assert torch.equal(moe.expert_ffn_shard(x, off, a), moe.expert_ffn_shard(x, off, b))
+
+
 @pytest.mark.parametrize("g", [0, 1, 2, 3])
 def test_ffn_shard_slice_of_full_weights(g):
     """moe_pack_weights cuts shard g (inner columns [g*f, (g+1)*f)) out of the full weights;
