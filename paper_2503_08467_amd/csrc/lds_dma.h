@@ -52,6 +52,12 @@ __device__ __forceinline__ void load_lds16(const unsigned char* base, uint32_t v
                  : "memory", "m0");
 }
 
+// The same from a 64-bit address per lane.
+__device__ __forceinline__ void load_lds16_at(const unsigned char* addr, uint32_t lds_addr) {
+    lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(addr) : "memory", "m0");
+}
+
 // LDS byte address of a shared-memory pointer (wave-uniform).
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
     return __builtin_amdgcn_readfirstlane(

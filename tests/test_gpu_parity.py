@@ -359,6 +359,30 @@ def test_streamed_weights(dtype, act, counts, h, f):
         assert rowwise(np_of(got), wt[:, None] * ref[inv]) <= tol
 
 
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+@pytest.mark.parametrize("h", [8, 24, 40, 776, 1000])
+@pytest.mark.parametrize("counts", [[600, 0, 130], [3, 40]])
+def test_hidden_size_off_the_k_block(counts, h, act):
+    """h not a multiple of 32: K ends inside a block, and the chunks past it are zeros for both
+    operands -- a NaN in one row reaches no other (its row and the weights' next rows follow
+    where a chunk past the end would be read)."""
+    rng = np.random.default_rng(h + len(counts))
+    x, w1, w3, w2, offsets = _ffn_case(rng, counts, h, 150, act, "bf16")
+    bad = 2  # its neighbours' last chunks border on it
+    x[bad] = 0
+    ref = oracle.expert_ffn(x, offsets, w1, w3, w2, act)
+    dt = torch.bfloat16
+    packed = moe.pack_weights(to_dev(w1, dt), to_dev(w2, dt), to_dev(w3, dt), act=act)
+    od = to_dev(offsets, torch.int32)
+    clean = moe.expert_ffn_shard(to_dev(x, dt), od, packed)
+    x[bad] = np.nan
+    xd, src = to_dev(x, dt), torch.arange(len(x), dtype=torch.int32, device="cuda")
+    keep = torch.arange(len(x), device="cuda") != bad
+    for y in (moe.expert_ffn_shard(xd, od, packed), moe.expert_ffn_shard_gather(xd, src, od, packed)):
+        assert torch.equal(y[keep], clean[keep]) and bool(y[bad].isnan().all())
+    assert rowwise(np_of(clean), ref) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("act", ["gelu", "gelu_tanh", "swiglu"])
 @pytest.mark.parametrize("counts,h,f", [
     ([600], 72, 1536),                # down-projection on 256 x 256 tiles: N below one tile
