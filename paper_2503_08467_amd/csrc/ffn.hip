@@ -1829,13 +1829,28 @@ hipError_t run_bf16_lds(GroupedGemm g, int64_t A_max, hipStream_t s) {
 // 49.7 through a register-staged kernel).  The
 // down-projection's K is fp, always a multiple of 128.
 //
-// When the down-projection's tiles fit on the CUs in one round even 384 columns wide (few
-// rows, e.g. a top-1 layer of a few thousand tokens or a decode batch), it runs 128 x 384
-// tiles, one workgroup per CU with 96 KiB of stages: every tile then streams its weights
-// with more bytes in flight instead of a third of the CUs taking a second tile.  That
-// workgroup has 8 waves (2 x 4, each 64 x 96), two per SIMD, so that one wave's LDS reads,
-// loads and barrier waits overlap the other's MFMAs.  Each output element's K sum is the
-// same in any of these shapes.
+// Few tiles leave CUs idle and few bytes in flight, so such calls take smaller ones.  Measured
+// (us, up / down; each output element's K sum is the same in any shape):
+// - experts that average at most 48 rows, 64 x 256: 64 experts (1024 x 1024) 2000 rows 34 / 35
+//   -> 30 / 30, 3000 rows 42 / 42 -> 38 / 37; 4000 rows would lose (35 / 32 -> 40 / 39);
+// - at most 5/8 of a 128 x 256 tile per CU, 128 x 128 in four stages, three workgroups a CU: 16
+//   experts (1408 x 1024) 2000 rows 34 / 27 -> 25 / 19; 8 experts (3072 x 384 SwiGLU) 4000 rows up
+//   65 -> 39; 24 experts (776 x 1365) 3062 rows down 33 -> 22; at 3/4 of a tile 31 -> 34, 25 -> 28;
+// - at most 1/4, 64 x 128 for the up-projection: 4 experts (1728 x 1520) 823 rows 40 -> 18 (24 at
+//   128 x 128).
+// When the down-projection's tiles fit on the CUs in one round even 384 columns wide, and those
+// waste no more columns than 256-wide ones, it runs 128 x 384 tiles, one workgroup per CU with
+// 96 KiB of stages: every tile then streams its weights with more bytes in flight instead of a
+// third of the CUs taking a second tile (64 experts, 3072 x 768, 8192 rows 108 -> 89; 1024 columns
+// in three would lose: 26 -> 30).  That workgroup has 8 waves (2 x 4, each 64 x 96), two per SIMD, so
+// that one wave's LDS reads, loads and barrier waits overlap the other's MFMAs.
+bool thin_experts(int64_t A_max, int E) { return A_max <= 48 * static_cast<int64_t>(E); }
+
+// Tiles of 128 rows with half an empty row tile per expert.
+double expected_tiles(int64_t A_max, int E, int64_t n_tiles) {
+    return (static_cast<double>(A_max) / 128 + 0.5 * E) * static_cast<double>(n_tiles);
+}
+
 template <int EPI>
 hipError_t run_up_pairs(GroupedGemm g, int64_t A_max, hipStream_t s) {
     static const hipError_t attr =
@@ -1943,6 +1958,12 @@ hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
     if constexpr (kUp) {
         if (turns_up(g, A_max, static_cast<int>(ceil_div(g.N, EPI == kEpiSwiglu ? 128 : 256))))
             return run_turns<EPI, OB>(g, A_max, s);
+        if (g.K % 32 == 0) {
+            if (thin_experts(A_max, g.E)) return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
+            const double tiles = expected_tiles(A_max, g.E, ceil_div(g.N, EPI == kEpiSwiglu ? 128 : 256));
+            if (4 * tiles <= device_cus()) return run_bf16_lds<64, 128, 32, 3, EPI, OB>(g, A_max, s);
+            if (8 * tiles <= 5 * device_cus()) return run_bf16_lds<128, 128, 32, 4, EPI, OB>(g, A_max, s);
+        }
         // activation rows in 128-byte pieces when K allows it (see gemm_up_pairs)
         if constexpr (OB) {
             if (g.K % 64 == 0) return run_up_pairs<EPI>(g, A_max, s);
@@ -1952,7 +1973,11 @@ hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
     } else {
         if (g.K % 32 != 0) return hipErrorInvalidValue;  // not reachable through the C ABI (fp % 128 == 0)
         if (turns_down(g, A_max)) return run_turns<EPI, OB>(g, A_max, s);
-        if (g.N >= 384 && row_tile_bound(A_max, g.E, 128) * ceil_div(g.N, 384) <= device_cus())
+        if (thin_experts(A_max, g.E)) return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
+        if (8 * expected_tiles(A_max, g.E, ceil_div(g.N, 256)) <= 5 * device_cus())
+            return run_bf16_lds<128, 128, 32, 4, EPI, OB>(g, A_max, s);
+        if (ceil_div(g.N, 384) * 384 <= ceil_div(g.N, 256) * 256 &&
+            row_tile_bound(A_max, g.E, 128) * ceil_div(g.N, 384) <= device_cus())
             return run_bf16_lds<128, 384, 32, 3, EPI, OB, 4>(g, A_max, s);
         return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);
     }

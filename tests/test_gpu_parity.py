@@ -383,6 +383,33 @@ def test_hidden_size_off_the_k_block(counts, h, act):
     assert rowwise(np_of(clean), ref) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+@pytest.mark.parametrize("counts,h,f", [
+    ([37] * 14 + [64, 65, 0], 96, 200),   # at most 48 rows per expert: 64 x 256 tiles
+    ([600, 129, 1], 160, 300),            # at most a quarter of a tile per CU: 64 x 128 up
+    ([900, 900, 127, 700], 520, 1300),    # ... 5/8: 128 x 128, four stages
+    ([3000, 2500, 1], 768, 640),          # down 128 x 384
+    ([128] * 120, 264, 136),              # many tiles: 128 x 256
+])
+def test_tile_shapes_agree(counts, h, f, act):
+    """The tile is chosen from the call's rows, experts and columns; a launch per expert chooses
+    by that expert alone.  Bits agree, and a sample of rows matches the oracle."""
+    rng = np.random.default_rng(sum(counts) + h)
+    x, w1, w3, w2, offsets = _ffn_case(rng, counts, h, f, act, "bf16")
+    dt = torch.bfloat16
+    packed = moe.pack_weights(to_dev(w1, dt), to_dev(w2, dt), to_dev(w3, dt), act=act)
+    xd, od = to_dev(x, dt), to_dev(offsets, torch.int32)
+    for out in (torch.bfloat16, torch.float32):
+        y = moe.expert_ffn_shard(xd, od, packed, out_dtype=out)
+        assert torch.equal(y, moe.expert_ffn_shard_per_expert(xd, od, packed, out_dtype=out))
+    # the first and last 20 rows of every expert
+    rows = [np.unique(np.r_[a:min(a + 20, b), max(a, b - 20):b]) for a, b in zip(offsets[:-1], offsets[1:])]
+    sub = np.concatenate(rows).astype(np.int64)
+    soff = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ref = oracle.expert_ffn(x[sub], soff, w1, w3, w2, act)
+    assert rowwise(np_of(y)[sub], ref) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("act", ["gelu", "gelu_tanh", "swiglu"])
 @pytest.mark.parametrize("counts,h,f", [
     ([600], 72, 1536),                # down-projection on 256 x 256 tiles: N below one tile
