@@ -484,8 +484,10 @@ void gemm_bf16_lds(GroupedGemm g) {
     // ---- load cursor: tile lt, K step lk, scalar bases of the tile's rows at K = 0
     int lt = t_first, lk = 0;
     const unsigned char *src_a = nullptr, *src_b0 = nullptr, *src_b1 = nullptr;
+    TileGeom lg;  // of the tile being loaded
     auto set_tile = [&](int L) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, L);
+        lg = tile_geom<BM, BN>(g, tiles, L);
+        const TileGeom& t = lg;
         const int64_t rb = kUp ? 2 * static_cast<int64_t>(g.K) : 64;
         if (kUp && g.gather) {
             // this lane's activation rows come from the gathered source rows (the index
@@ -576,7 +578,8 @@ void gemm_bf16_lds(GroupedGemm g) {
     constexpr bool kAccInAgpr = S::kPerCU == 1;
     int consumed = 0;
     for (int ct = t_first; ct < t_end; ct += nslot) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, ct);
+        // the loads are NS - 1 stages ahead: still in this tile unless its K is that short
+        const TileGeom t = nk >= NS ? lg : tile_geom<BM, BN>(g, tiles, ct);
         // Row blocks of this wave that hold valid rows.  Valid rows start at the tile's first
         // row unless the tile was shifted back at the end of the buffer; then all count.  The
         // count is rounded up to MI / 2 or MI so that three loop bodies cover every case.
@@ -717,8 +720,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
 
     int lt = t_first, lk = 0;
     const unsigned char *src_a = nullptr, *src_b0 = nullptr, *src_b1 = nullptr;
+    TileGeom lg;  // of the tile being loaded
     auto set_tile = [&](int L) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, L);
+        lg = tile_geom<BM, BN>(g, tiles, L);
+        const TileGeom& t = lg;
 #pragma unroll
         for (int j = 0; j < LPA; ++j) {
             const int R = (j * 4 + wave) * 8 + (lane >> 3);
@@ -794,7 +799,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
 
     int consumed = 0;
     for (int ct = t_first; ct < t_end; ct += nslot) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, ct);
+        const TileGeom t = nk >= NS ? lg : tile_geom<BM, BN>(g, tiles, ct);  // as in gemm_bf16_lds
         int nv = MI;
         if (t.row_base == t.row0) {
             const int64_t left = t.row_end - (t.row0 + wm * (BM / 2));
@@ -1311,8 +1316,10 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
     // ---- load cursor: work item li, K step lk, scalar bases of the item's rows
     int li = t_first, lk = 0;
     const unsigned char *src_a = nullptr, *src_b0 = nullptr, *src_b1 = nullptr;
+    TileGeom lg;  // of the item being loaded
     auto set_item = [&](int L) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, L / ks);
+        lg = tile_geom<BM, BN>(g, tiles, L / ks);
+        const TileGeom& t = lg;
         const int64_t k0 = static_cast<int64_t>(L % ks) * nk * kF2BK;  // first K value of the item
         if (g.gather) {
             // absolute source row (T h 4 < 4 GiB is checked by the host)
@@ -1351,7 +1358,7 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
     const int l32 = lane & 31, lhi = lane >> 5;
     int consumed = 0;
     for (int L = t_first; L < t_end; L += nslot) {
-        const TileGeom t = tile_geom<BM, BN>(g, tiles, L / ks);
+        const TileGeom t = nk >= NS ? lg : tile_geom<BM, BN>(g, tiles, L / ks);  // as in gemm_bf16_lds
         f32x16_t acc[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
@@ -1972,12 +1979,16 @@ hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
         return run_bf16_lds<128, 256, 32, 3, EPI, OB, 2, true>(g, A_max, s);
     } else {
         if (g.K % 32 != 0) return hipErrorInvalidValue;  // not reachable through the C ABI (fp % 128 == 0)
-        if (turns_down(g, A_max)) return run_turns<EPI, OB>(g, A_max, s);
+        const bool fits_384 = ceil_div(g.N, 384) * 384 <= ceil_div(g.N, 256) * 256 &&
+                              row_tile_bound(A_max, g.E, 128) * ceil_div(g.N, 384) <= device_cus();
+        // 32 experts (1568 x 640), 9542 rows: the layer 101 us at 384 columns, 105 in turns; from
+        // 375 rows per expert turns win there too (48.6 -> 45.2)
+        if (turns_down(g, A_max) && !(fits_384 && A_max < 320 * static_cast<int64_t>(g.E)))
+            return run_turns<EPI, OB>(g, A_max, s);
         if (thin_experts(A_max, g.E)) return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
         if (8 * expected_tiles(A_max, g.E, ceil_div(g.N, 256)) <= 5 * device_cus())
             return run_bf16_lds<128, 128, 32, 4, EPI, OB>(g, A_max, s);
-        if (ceil_div(g.N, 384) * 384 <= ceil_div(g.N, 256) * 256 &&
-            row_tile_bound(A_max, g.E, 128) * ceil_div(g.N, 384) <= device_cus())
+        if (fits_384)
             return run_bf16_lds<128, 384, 32, 3, EPI, OB, 4>(g, A_max, s);
         return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);
     }

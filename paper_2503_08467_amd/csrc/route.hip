@@ -307,7 +307,7 @@ template <int NE>
 constexpr int route_ldw() { return NE * 16 + 4; }  // 16 tokens' 16-byte runs fall on all banks
 
 template <typename Tin, int NE, int MT, bool RAG>
-__global__ __launch_bounds__(route_waves<NE>() * kWave, NE <= 8 ? 2 : 1) void route_kernel(const Tin* __restrict__ x,
+__global__ __launch_bounds__(route_waves<NE>() * kWave, MT == 2 && NE <= 4 ? 4 : NE <= 8 ? 2 : 1) void route_kernel(const Tin* __restrict__ x,
                                                                const Tin* __restrict__ wg, int64_t T, int h,
                                                                int E, int k, const float* __restrict__ bias,
                                                                int64_t bias_stride, int renorm,
@@ -315,7 +315,8 @@ __global__ __launch_bounds__(route_waves<NE>() * kWave, NE <= 8 ? 2 : 1) void ro
                                                                FusedDispatch fd) {
     constexpr bool kBf = std::is_same<Tin, bf16_t>::value;
     constexpr int ES = sizeof(Tin), EP = NE * 16, RW = route_waves<NE>(), LDW = route_ldw<NE>(), kTok = 16 * MT;
-    constexpr int U = 16 / (NE + MT) > 8 ? 8 : (16 / (NE + MT) < 1 ? 1 : 16 / (NE + MT));
+    constexpr int kU = (MT == 1 ? 16 : 10) / (NE + MT);
+    constexpr int U = kU > 8 ? 8 : (kU < 1 ? 1 : kU);
     constexpr int NV = EP / 8;             // experts per lane in the epilogue
     extern __shared__ __align__(16) float part[];  // [RW][kTok][LDW] partial logits
     const int lane = threadIdx.x & (kWave - 1);
@@ -683,9 +684,12 @@ hipError_t launch_route_mt(const void* x, int64_t T, int h, const void* wg, int 
     return go(&route_kernel<Tin, NE, MT, true>);
 }
 
-// Tokens per workgroup: 16 where the gate is small (4096 tokens, 32 experts 8.5 us at 32 tokens, 7.6
-// at 16), 32 where re-reading it per workgroup costs more (300 tokens, 60 experts 10.4 at 16, 9.7
-// at 32); a batch that one workgroup has to group (fd.counts) takes as many as it holds.
+// Tokens per workgroup: 16 while that fits the CUs in one round (2500 tokens, 8 experts, h = 4096
+// 10.1 us, 17.4 at 32 tokens) and the gate is small, 32 beyond (8192 tokens, 4 experts, h = 1024 9.7
+// at 16, 7.8 at 32; 30000 tokens, 16 experts, h = 768 37 and 20, 24 at 64) or where re-reading the
+// gate per workgroup costs more (300 tokens, 60 experts 10.4 and 9.7); a batch that one workgroup
+// has to group (fd.counts) takes as many as it holds.  With 32 tokens the stages are shorter, so
+// that two workgroups share a CU (30000 tokens: 24.6 us with one).
 template <typename Tin, int NE>
 hipError_t launch_route_ne(const void* x, int64_t T, int h, const void* wg, int E, int k, const float* bias,
                            int64_t bias_stride, int renorm, int32_t* idx, float* w, FusedDispatch fd, hipStream_t s) {
@@ -694,7 +698,7 @@ hipError_t launch_route_ne(const void* x, int64_t T, int h, const void* wg, int 
         if (fd.counts && T > 32) MOE_ROUTE(4);
     }
     if constexpr (NE <= 8) {
-        if (T > 16 && (fd.counts || NE > 2)) MOE_ROUTE(2);
+        if (T > 16 && (fd.counts || NE > 2 || T > 16 * 256)) MOE_ROUTE(2);
     }
     MOE_ROUTE(1);
 #undef MOE_ROUTE
