@@ -77,7 +77,7 @@ def measured_traffic(config: str):
 def is_ffn_kernel(name: str) -> bool:
     """The kernels of the expert step: the grouped GEMMs (up- and down-projection) and, for
     small bf16 calls whose down-projection splits K, the sum of its parts."""
-    return any(k in name for k in ("gemm_bf16", "gemm_up_pairs", "gemm_f32", "split_reduce"))
+    return any(k in name for k in ("gemm_bf16", "gemm_up_pairs", "gemm_turns", "gemm_stream", "gemm_f32", "split_reduce"))
 
 
 def is_layer_kernel(name: str) -> bool:
