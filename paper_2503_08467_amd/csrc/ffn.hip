@@ -292,33 +292,43 @@ struct RegTiles {
 // first row / column when the tile would run past the end of the buffer (so every load
 // stays inside it without a per-row check); the epilogue stores only the tile's own rows
 // [row0, row_end) and columns [n0, N).
+//
+// The load cursor keeps its tile's geometry in scalar registers through the K loop, so it is
+// four 32-bit values (a row of H takes at least 256 bytes, so a call that fits the memory has
+// fewer than 2^30 rows) and the two bases are derived from them.  With 64-bit rows and stored
+// bases gemm_up_pairs<GELU> spilled 30 scalar registers, 15 like this, and the small tiles some;
+// 32768 tokens (x 1024 -> 4096 -> 1024) 1263.8 -> 1256.1 us.
 struct TileGeom {
-    int64_t row0, row_end, row_base;
-    int n0, n_base, e;
+    int row0, row_end, n0, e;
 };
+
+template <int BM>
+__device__ __forceinline__ int row_base(const GroupedGemm& g, const TileGeom& t) {
+    return min(max(t.row0, 0), max(static_cast<int>(g.rows_max) - BM, 0));
+}
+template <int BN>
+__device__ __forceinline__ int n_base(const GroupedGemm& g, const TileGeom& t) {
+    return min(t.n0, max(g.N - BN, 0));
+}
 
 template <int BM, int BN, typename Tiles>
 __device__ __forceinline__ TileGeom tile_geom(const GroupedGemm& g, const Tiles& tiles, int L) {
     TileGeom t;
     t.e = __builtin_amdgcn_readfirstlane(tiles.find(L / g.n_tiles));
     const int first = __builtin_amdgcn_readfirstlane(tiles.start(t.e));
-    const int64_t seg0 = g.offsets[t.e], seg1 = g.offsets[t.e + 1];
+    const int seg0 = g.offsets[t.e], seg1 = g.offsets[t.e + 1];
     // tile L of the list is tile l of its expert's m x n_tiles tiles: groups of at most 8 row
     // tiles, as even as they go, column-major inside a group
-    const int m = static_cast<int>((seg1 - seg0 + BM - 1) / BM);
+    const int m = (seg1 - seg0 + BM - 1) / BM;
     const int l = L - first * g.n_tiles;
     const int gsz = (m + (m + 7) / 8 - 1) / ((m + 7) / 8);
     const int grp = l / (gsz * g.n_tiles);
     const int rem = l - grp * gsz * g.n_tiles;
     const int sz = min(gsz, m - grp * gsz);
     const int nt = rem / sz, mt = grp * gsz + rem - nt * sz;
-    t.row0 = seg0 + static_cast<int64_t>(mt) * BM;
-    t.row_end = seg1 < g.rows_max ? seg1 : g.rows_max;
-    const int64_t top = g.rows_max > BM ? g.rows_max - BM : 0;
-    t.row_base = t.row0 < 0 ? 0 : (t.row0 > top ? top : t.row0);
+    t.row0 = seg0 + mt * BM;
+    t.row_end = min(seg1, static_cast<int>(g.rows_max));
     t.n0 = nt * BN;
-    const int ntop = g.N > BN ? g.N - BN : 0;
-    t.n_base = t.n0 > ntop ? ntop : t.n0;
     return t;
 }
 
@@ -328,9 +338,8 @@ __device__ __forceinline__ TileGeom tile_geom(const GroupedGemm& g, const Tiles&
 template <int BM>
 __device__ __forceinline__ int tile_row_limit(const GroupedGemm& g, const TileGeom& t) {
     const int lim = static_cast<int>(g.rows_max < BM ? g.rows_max : BM) - 1;
-    if (t.row_base != t.row0) return lim;
-    const int64_t valid = t.row_end - t.row0;
-    return valid >= 1 && valid - 1 < lim ? static_cast<int>(valid - 1) : lim;
+    const int valid = t.row_end - t.row0;
+    return row_base<BM>(g, t) == t.row0 && valid >= 1 ? min(valid - 1, lim) : lim;
 }
 
 // Epilogue of one row of 32 x 32 blocks: rows [row, row + 32) of the wave (row: buffer row of
@@ -338,18 +347,18 @@ __device__ __forceinline__ int tile_row_limit(const GroupedGemm& g, const TileGe
 // K-blocked; otherwise row-major C (bf16 or fp32), with `scatter` w[t] * row into row
 // t = scatter[row].  Rows outside the tile's and columns outside [t.n0, N) are not stored.
 template <int EPI, bool OB, int NB, int NI, bool IN_AGPR, typename Acc>
-__device__ __forceinline__ void store_row_block(const GroupedGemm& g, const TileGeom& t, int64_t row, int n_lo,
+__device__ __forceinline__ void store_row_block(const GroupedGemm& g, const TileGeom& t, int row, int n_lo,
                                                 const Acc& acc) {
     constexpr bool kUp = EPI != kEpiNone;
     const int lane = threadIdx.x & 63;
-    const int64_t row_lo = t.row0 > 0 ? t.row0 : 0;
+    const int row_lo = max(t.row0, 0);
     int64_t r0 = row + (lane & 15), r1 = r0 + 16;  // the rows this lane stores
     const bool ok0 = r0 >= row_lo && r0 < t.row_end, ok1 = r1 >= row_lo && r1 < t.row_end;
     float scale = 1.f;
     if (!kUp && g.scatter) {
         // the grouped row's token and gate weight: looked up for the row whose sums this lane
         // holds (row + l % 32), then handed to the lanes that store it
-        const int64_t rs = row + (lane & 31);
+        const int rs = row + (lane & 31);
         const bool ok = rs >= row_lo && rs < t.row_end;
         const int64_t src = ok ? g.scatter[rs] : 0;
         const int tok = static_cast<int>(src < 0 ? 0 : (src >= g.c_rows ? g.c_rows - 1 : src));
@@ -498,7 +507,7 @@ void gemm_bf16_lds(GroupedGemm g) {
             for (int j = 0; j < kAJ; ++j) {
                 const int R = (j * NW + wave) * RPI + r_lane;
                 const int kc = c_lane ^ ((R >> SH) & (CPR - 1));
-                const int64_t src = source_row(g, t.row_base + min(R, a_lim));
+                const int64_t src = source_row(g, row_base<BM>(g, t) + min(R, a_lim));
                 voff[j] = static_cast<uint32_t>(src) * static_cast<uint32_t>(2 * g.K) + static_cast<uint32_t>(kc * 16);
             }
             src_a = uniform_ptr(g.a);
@@ -511,9 +520,9 @@ void gemm_bf16_lds(GroupedGemm g) {
                 const int kc = c_lane ^ ((R >> SH) & (CPR - 1));
                 voff[j] = static_cast<uint32_t>(min(R, a_lim)) * static_cast<uint32_t>(rb) + static_cast<uint32_t>(kc * 16);
             }
-            src_a = uniform_ptr(static_cast<const unsigned char*>(g.a) + t.row_base * rb);
+            src_a = uniform_ptr(static_cast<const unsigned char*>(g.a) + row_base<BM>(g, t) * rb);
         }
-        const int64_t boff = (t.e * g.b_estride) * 2 + static_cast<int64_t>(t.n_base) * (RM ? 2 * g.K : 64);
+        const int64_t boff = (t.e * g.b_estride) * 2 + static_cast<int64_t>(n_base<BN>(g, t)) * (RM ? 2 * g.K : 64);
         src_b0 = uniform_ptr(static_cast<const unsigned char*>(g.b) + boff);
         src_b1 = NB > 1 ? uniform_ptr(static_cast<const unsigned char*>(g.b2) + boff) : src_b0;
     };
@@ -584,8 +593,8 @@ void gemm_bf16_lds(GroupedGemm g) {
         // row unless the tile was shifted back at the end of the buffer; then all count.  The
         // count is rounded up to MI / 2 or MI so that three loop bodies cover every case.
         int nv = MI;
-        if (t.row_base == t.row0) {
-            const int64_t left = t.row_end - (t.row0 + wm * (BM / 2));
+        if (row_base<BM>(g, t) == t.row0) {
+            const int left = t.row_end - (t.row0 + wm * (BM / 2));
             nv = left <= 0 ? 0 : (left > (MI / 2) * 32 ? MI : MI / 2);
         }
         nv = __builtin_amdgcn_readfirstlane(nv);
@@ -656,8 +665,8 @@ void gemm_bf16_lds(GroupedGemm g) {
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             if (i >= nv) break;  // no valid row in this block or any later one
-            store_row_block<EPI, OB, NB, NI, kAccInAgpr>(g, t, t.row_base + wm * (BM / 2) + i * 32,
-                                                         t.n_base + wn * (BN / WN), acc[i]);
+            store_row_block<EPI, OB, NB, NI, kAccInAgpr>(g, t, row_base<BM>(g, t) + wm * (BM / 2) + i * 32,
+                                                         n_base<BN>(g, t) + wn * (BN / WN), acc[i]);
         }
     }
 }
@@ -731,11 +740,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
             // gathered: absolute source row (T h s < 4 GiB is checked by the host); else the
             // tile's base carries the row offset
             const int a_lim_t = tile_row_limit<BM>(g, t);
-            const int64_t r = g.gather ? source_row(g, t.row_base + min(R, a_lim_t)) : min(R, a_lim_t);
+            const int64_t r = g.gather ? source_row(g, row_base<BM>(g, t) + min(R, a_lim_t)) : min(R, a_lim_t);
             voffA[j] = static_cast<uint32_t>(r) * static_cast<uint32_t>(2 * g.K) + static_cast<uint32_t>(c * 16);
         }
-        src_a = uniform_ptr(static_cast<const unsigned char*>(g.a) + (g.gather ? 0 : t.row_base * 2 * g.K));
-        const int64_t boff = (t.e * g.b_estride) * 2 + static_cast<int64_t>(t.n_base) * 64;
+        src_a = uniform_ptr(static_cast<const unsigned char*>(g.a) + (g.gather ? 0 : static_cast<int64_t>(row_base<BM>(g, t)) * 2 * g.K));
+        const int64_t boff = (t.e * g.b_estride) * 2 + static_cast<int64_t>(n_base<BN>(g, t)) * 64;
         src_b0 = uniform_ptr(static_cast<const unsigned char*>(g.b) + boff);
         src_b1 = NB > 1 ? uniform_ptr(static_cast<const unsigned char*>(g.b2) + boff) : src_b0;
     };
@@ -801,8 +810,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
     for (int ct = t_first; ct < t_end; ct += nslot) {
         const TileGeom t = nk >= NS ? lg : tile_geom<BM, BN>(g, tiles, ct);  // as in gemm_bf16_lds
         int nv = MI;
-        if (t.row_base == t.row0) {
-            const int64_t left = t.row_end - (t.row0 + wm * (BM / 2));
+        if (row_base<BM>(g, t) == t.row0) {
+            const int left = t.row_end - (t.row0 + wm * (BM / 2));
             nv = left <= 0 ? 0 : (left > (MI / 2) * 32 ? MI : MI / 2);
         }
         nv = __builtin_amdgcn_readfirstlane(nv);
@@ -867,8 +876,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             if (i >= nv) break;
-            store_row_block<EPI, true, NB, NI, false>(g, t, t.row_base + wm * (BM / 2) + i * 32,
-                                                      t.n_base + wn * (BN / 2), acc[i]);
+            store_row_block<EPI, true, NB, NI, false>(g, t, row_base<BM>(g, t) + wm * (BM / 2) + i * 32,
+                                                      n_base<BN>(g, t) + wn * (BN / 2), acc[i]);
         }
     }
 }
@@ -929,13 +938,10 @@ __global__ __launch_bounds__(512, 2) void gemm_turns(GroupedGemm g) {
         TileGeom t = tile_geom<BM, BN>(g, tiles, t_begin + whole + r);
         if (parts > 1) {
             // rows [p q, (p + 1) q) of the tile's valid ones, q a multiple of 32
-            const int64_t valid = t.row_end - t.row0 < BM ? t.row_end - t.row0 : BM;
-            const int64_t q = (valid + 32 * parts - 1) / (32 * parts) * 32;
-            const int64_t end = t.row0 + (p + 1) * q;
+            const int valid = min(t.row_end - t.row0, BM);
+            const int q = (valid + 32 * parts - 1) / (32 * parts) * 32;
+            t.row_end = min(t.row0 + (p + 1) * q, t.row_end);
             t.row0 += p * q;
-            t.row_end = end < t.row_end ? end : t.row_end;
-            const int64_t top = g.rows_max > BM ? g.rows_max - BM : 0;
-            t.row_base = t.row0 > top ? top : t.row0;
         }
         return t;
     };
@@ -968,12 +974,12 @@ __global__ __launch_bounds__(512, 2) void gemm_turns(GroupedGemm g) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int R = min((j * 8 + wave) * 16 + r_lane, a_lim);
-            const int64_t r = (kUp && g.gather) ? source_row(g, t.row_base + R) : R;
+            const int64_t r = (kUp && g.gather) ? source_row(g, row_base<BM>(g, t) + R) : R;
             voff[j] = static_cast<uint32_t>(r) * rb + kc16;
         }
         src_a = uniform_ptr(static_cast<const unsigned char*>(g.a) +
-                            ((kUp && g.gather) ? 0 : t.row_base * static_cast<int64_t>(rb)));
-        const int64_t boff = (t.e * g.b_estride) * 2 + static_cast<int64_t>(t.n_base) * 64;
+                            ((kUp && g.gather) ? 0 : row_base<BM>(g, t) * static_cast<int64_t>(rb)));
+        const int64_t boff = (t.e * g.b_estride) * 2 + static_cast<int64_t>(n_base<BN>(g, t)) * 64;
         src_b0 = uniform_ptr(static_cast<const unsigned char*>(g.b) + boff);
         src_b1 = NB > 1 ? uniform_ptr(static_cast<const unsigned char*>(g.b2) + boff) : src_b0;
     };
@@ -1015,9 +1021,9 @@ __global__ __launch_bounds__(512, 2) void gemm_turns(GroupedGemm g) {
         // the loads are NS - 1 stages ahead: still in this item unless it is that short
         const TileGeom t = nk >= NS ? lg : item_geom(ci);
         int nv = MI;
-        if (t.row_base == t.row0) {
-            const int64_t left = t.row_end - t.row0 - 32 * grp;
-            nv = left <= 0 ? 0 : (left >= BM - 64 ? MI : static_cast<int>((left + 63) >> 6));
+        if (row_base<BM>(g, t) == t.row0) {
+            const int left = t.row_end - t.row0 - 32 * grp;
+            nv = left <= 0 ? 0 : (left >= BM - 64 ? MI : (left + 63) >> 6);
         }
         nv = __builtin_amdgcn_readfirstlane(nv);
 
@@ -1087,7 +1093,7 @@ __global__ __launch_bounds__(512, 2) void gemm_turns(GroupedGemm g) {
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             if (i >= nv) break;
-            store_row_block<EPI, OB, NB, NI, false>(g, t, t.row_base + (2 * i + grp) * 32, t.n_base + wn * (BN / 4),
+            store_row_block<EPI, OB, NB, NI, false>(g, t, row_base<BM>(g, t) + (2 * i + grp) * 32, n_base<BN>(g, t) + wn * (BN / 4),
                                                     acc[i]);
         }
     }
@@ -1323,14 +1329,14 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
         const int64_t k0 = static_cast<int64_t>(L % ks) * nk * kF2BK;  // first K value of the item
         if (g.gather) {
             // absolute source row (T h 4 < 4 GiB is checked by the host)
-            const int64_t src = source_row(g, t.row_base + ra);
+            const int64_t src = source_row(g, row_base<BM>(g, t) + ra);
             voff[0] = static_cast<uint32_t>(src) * static_cast<uint32_t>(4 * g.K) + kca;
             src_a = uniform_ptr(static_cast<const float*>(g.a) + k0);
         } else {
             voff[0] = static_cast<uint32_t>(ra) * static_cast<uint32_t>(4 * g.K) + kca;
-            src_a = uniform_ptr(static_cast<const float*>(g.a) + t.row_base * g.K + k0);
+            src_a = uniform_ptr(static_cast<const float*>(g.a) + static_cast<int64_t>(row_base<BM>(g, t)) * g.K + k0);
         }
-        const int64_t boff = t.e * g.b_estride + static_cast<int64_t>(t.n_base) * g.K + k0;
+        const int64_t boff = t.e * g.b_estride + static_cast<int64_t>(n_base<BN>(g, t)) * g.K + k0;
         src_b0 = uniform_ptr(static_cast<const float*>(g.b) + boff);
         src_b1 = NB > 1 ? uniform_ptr(static_cast<const float*>(g.b2) + boff) : src_b0;
     };
@@ -1356,6 +1362,14 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
     for (int st = 0; st < NS - 1; ++st) issue_next();
 
     const int l32 = lane & 31, lhi = lane >> 5;
+    // byte offsets of this lane's fragments in a stage
+    int xoff[kF2BK / 8], woff[kF2BK / 8];
+#pragma unroll
+    for (int q = 0; q < kF2BK / 8; ++q) {
+        const int slot = 2 * q + lhi, Rw = BM + 32 * wave + l32;
+        xoff[q] = l32 * 128 + ((slot ^ ((l32 >> 1) & 7)) << 4);
+        woff[q] = Rw * 128 + ((slot ^ ((Rw >> 1) & 7)) << 4);
+    }
     int consumed = 0;
     for (int L = t_first; L < t_end; L += nslot) {
         const TileGeom t = nk >= NS ? lg : tile_geom<BM, BN>(g, tiles, L / ks);  // as in gemm_bf16_lds
@@ -1375,13 +1389,11 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
             const unsigned char* st = smem_raw + (consumed % NS) * kStageBytes;
 #pragma unroll
             for (int q = 0; q < kF2BK / 8; ++q) {
-                const int slot = 2 * q + lhi;
-                const float4 xf = *reinterpret_cast<const float4*>(st + l32 * 128 + ((slot ^ ((l32 >> 1) & 7)) << 4));
+                const float4 xf = *reinterpret_cast<const float4*>(st + xoff[q]);
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
-                    const int Rw = BM + nb * BN + 32 * wave + l32;
-                    const float4 wf =
-                        *reinterpret_cast<const float4*>(st + Rw * 128 + ((slot ^ ((Rw >> 1) & 7)) << 4));
+                    // the next matrix's rows are BN further: the same swizzle
+                    const float4 wf = *reinterpret_cast<const float4*>(st + woff[q] + nb * BN * 128);
                     acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf.x, xf.x, acc[nb], 0, 0, 0);
                     acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf.y, xf.y, acc[nb], 0, 0, 0);
                     acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf.z, xf.z, acc[nb], 0, 0, 0);
@@ -1401,10 +1413,9 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
 
         // ---- epilogue.  Lane: activation row row_base + l32; register 4 q + c: output column
         // n_base + 32 wave + 8 q + 4 lhi + c.
-        const int64_t row = t.row_base + l32;
-        const int64_t row_lo = t.row0 > 0 ? t.row0 : 0;
-        const bool row_ok = row >= row_lo && row < t.row_end;
-        const int cb = t.n_base + 32 * wave + 4 * lhi;
+        const int64_t row = row_base<BM>(g, t) + l32;
+        const bool row_ok = row >= max(t.row0, 0) && row < t.row_end;
+        const int cb = n_base<BN>(g, t) + 32 * wave + 4 * lhi;
         if (ks > 1) {
             // a K part: its fp32 sums go to partial[part][row][N], the reduce kernel finishes
             float* const dst = g.partial + static_cast<int64_t>(L % ks) * g.rows_max * g.N;
@@ -1505,9 +1516,9 @@ __global__ __launch_bounds__(512, MR == 1 ? 4 : 2) void gemm_stream(GroupedGemm 
     const uint32_t a_row = a_blocked ? 64u : static_cast<uint32_t>(kbytes);
     const int64_t a_step = a_blocked ? g.rows_max * 64 : 64;
     const bool gathered = kUp && g.gather;
-    const unsigned char* abase = uniform_ptr(static_cast<const unsigned char*>(g.a) + (gathered ? 0 : t.row0 * a_row));
+    const unsigned char* abase = uniform_ptr(static_cast<const unsigned char*>(g.a) + (gathered ? 0 : static_cast<int64_t>(t.row0) * a_row));
     uint32_t aoff[MR];
-    const int valid = static_cast<int>(t.row_end - t.row0 < BM ? t.row_end - t.row0 : BM);
+    const int valid = min(t.row_end - t.row0, BM);
     if (valid <= 0) return;
 #pragma unroll
     for (int m = 0; m < MR; ++m) {
@@ -1604,7 +1615,7 @@ __global__ __launch_bounds__(512, MR == 1 ? 4 : 2) void gemm_stream(GroupedGemm 
             }
             const int n = t.n0 + c;
             if (16 * m + r >= valid || n >= g.N) continue;
-            int64_t row = t.row0 + 16 * m + r;
+            int64_t row = static_cast<int64_t>(t.row0) + 16 * m + r;
             if (!kUp && g.partial) {  // whole sums in fp32, for split_combine
                 *reinterpret_cast<float2*>(g.partial + row * g.N + n) = v;
                 continue;
