@@ -76,7 +76,7 @@ def measured_traffic(config: str):
 
 def is_ffn_kernel(name: str) -> bool:
     """The kernels of the expert step: the grouped GEMMs (up- and down-projection) and, for
-    small bf16 calls whose down-projection splits K, the sum of its parts."""
+    small fp32 calls whose down-projection splits K, the sum of its parts."""
     return any(k in name for k in ("gemm_bf16", "gemm_up_pairs", "gemm_turns", "gemm_stream", "gemm_f32", "split_reduce"))
 
 
@@ -97,12 +97,20 @@ def stage_bytes(cfg, fused_gather: bool, top1_fused: bool, bias_per_row: bool) -
     return {"route": route, "dispatch": dispatch, "combine": combine}
 
 
+# Where each grouped GEMM has its epilogue among its template arguments (3: no activation).
+EPILOGUE_ARG = {"gemm_bf16_lds": 4, "gemm_up_pairs": 0, "gemm_turns": 0, "gemm_stream": 1, "gemm_f32": 0,
+                "gemm_f32_lds": 0}
+
+
 def ffn_matrix(name: str) -> str:
-    """"down" for the down-projection launches (epilogue template argument 3, no activation;
-    the sum of its K parts), else "up"."""
+    """"down" for the down-projection launches (an epilogue without an activation; the sum of its
+    K parts), else "up"."""
     if "split_reduce" in name:
         return "down"
-    return "down" if re.search(r"<(?:[^>]*, )?3, (?:true|false)(?:, \d+)?>", name) else "up"
+    m = re.search(r"\b(gemm_\w+)<([^>]*)>", name)
+    if not m or m.group(1) not in EPILOGUE_ARG:
+        raise ValueError(f"not a kernel of the expert step: {name}")
+    return "down" if m.group(2).split(",")[EPILOGUE_ARG[m.group(1)]].strip() == "3" else "up"
 
 
 def summarize_counters(config: str, fetch_dir: str, write_dir: str, probe_mib: int):
@@ -513,8 +521,8 @@ def main():
              "frac": round(achieved_tflops / peak_tf, 4)})
     roof["traffic"] = measured_traffic(args.config)
     roof["kernel"] = ("moe_expert_ffn_shard" + ("_top1" if top1_fused else "" if args.unfused_gather else "_gather") +
-                      " (grouped GEMM1+act and GEMM2, one launch each; calls of at most 512 bf16 rows"
-                      " add one launch that sums the K parts of GEMM2); HIP events around the call in a "
+                      " (grouped GEMM1+act and GEMM2, one launch each; fp32 calls of at most 1024 rows that do not"
+                      " stream their weights add one launch that sums the K parts of GEMM2); HIP events around the call in a "
                       "second pass of as many cold-cache steps as the timed ones, made of the layer's calls "
                       "one by one (the timed steps carry no event inside them)")
     roof["algorithmic"] = {"bytes": ffn_bytes, "flops": ffn_flops, "touched_experts": touched,

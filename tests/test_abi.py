@@ -197,6 +197,32 @@ def test_bench_names_the_expert_step_kernels():
     assert not bench.is_layer_kernel("void at::native::vectorized_elementwise_kernel<4, at::native::neg_kernel>")
 
 
+def test_bench_tells_the_matrices_of_every_built_gemm():
+    # every grouped-GEMM instantiation of the built library, by the names a profile shows
+    import shutil
+    import subprocess
+    import bench
+    if not shutil.which("nm"):
+        pytest.skip("no nm")
+    syms = subprocess.run(["nm", "-C", moe.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    names = {line.split("__device_stub__", 1)[1] for line in syms.splitlines() if "__device_stub__gemm_" in line}
+    assert names
+    seen = set()
+    for n in names:
+        kernel, args = re.match(r"(\w+)<([^>]*)>", n).groups()
+        args = [a.strip() for a in args.split(",")]
+        name = "void moe::(anonymous namespace)::" + n
+        assert bench.is_ffn_kernel(name)
+        # the kernel templates: <BM, BW, BK, NS, EPI, ...>, <T, EPI, ...> and <EPI, ...>
+        epi = args[4] if kernel == "gemm_bf16_lds" else args[1] if kernel == "gemm_stream" else args[0]
+        assert bench.ffn_matrix(name) == ("down" if epi == "3" else "up"), n
+        seen.add((kernel, epi == "3"))
+    for kernel in ("gemm_bf16_lds", "gemm_turns", "gemm_stream", "gemm_f32_lds"):
+        assert {(kernel, False), (kernel, True)} <= seen, kernel
+    with pytest.raises(ValueError):
+        bench.ffn_matrix("void moe::(anonymous namespace)::combine_kernel<true, true>(void const*)")
+
+
 def test_bench_stage_bytes():
     """Algorithmic bytes of the non-GEMM steps: inputs read once, outputs written once."""
     import bench
