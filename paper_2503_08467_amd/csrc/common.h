@@ -65,30 +65,32 @@ __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
 // Fast activations for the bf16 epilogues (their error is far below bf16 rounding).
 //
 // GELU(u) = u Phi(u) = max(u, 0) - |u| Q(|u|) with Q(a) = Phi(-a) = 2^p(a); p, the base-2
-// logarithm of the normal tail, is smooth, and its degree-8 fit here (weighted least squares
-// on [0, 6], the weight a Q(a) being what an error of p moves the result by, reweighted until
-// the largest errors are level) leaves |GELU error| <= 2.4e-7 in fp32 (3.0e-8 root mean square
-// over N(0, 1)) and 1.2e-4 relative in the negative tail; past 6 the leading coefficient takes
-// 2^p to 0 (2^p is exact to 0.2 % at 7, where it is 1e-12).  One exponential and ten plain
-// instructions, where Abramowitz & Stegun 7.1.26 (3.3e-7, 5.4e-8, and 3.6e-3 in the tail)
-// took a reciprocal, an exponential and fourteen.
+// logarithm of the normal tail, is smooth, and its degree-8 fit here (least largest error of
+// a Q(a) over [0, 9], by linear programming, subject to the relative errors of the tail) leaves
+// |GELU error| <= 2.6e-7 in fp32 (3.9e-8 root mean square over N(0, 1)) and in the negative
+// tail relative errors of at most 2.6e-3 down to -7 and 1.2e-2 down to -9, where the values
+// are 1e-18; past that the leading coefficient takes 2^p to 0.  One exponential and ten plain
+// instructions, where Abramowitz & Stegun 7.1.26 (3.3e-7, 5.5e-8, 6.5e-3 and 1.5e-2) took a
+// reciprocal, an exponential and fourteen.
 __device__ __forceinline__ float act_gelu_fast(float u) {
     const float a = fabsf(u);
-    float p = -4.57867628e-07f;
-    p = fmaf(p, a, 7.50441768e-06f);
-    p = fmaf(p, a, -1.39624080e-05f);
-    p = fmaf(p, a, -6.20413106e-04f);
-    p = fmaf(p, a, 7.82226119e-03f);
-    p = fmaf(p, a, -5.31633273e-02f);
-    p = fmaf(p, a, -4.58897173e-01f);
-    p = fmaf(p, a, -1.15117216e+00f);
-    p = fmaf(p, a, -9.99995291e-01f);
+    float p = -1.76333070e-07f;
+    p = fmaf(p, a, 2.71696660e-06f);
+    p = fmaf(p, a, 1.74325122e-05f);
+    p = fmaf(p, a, -7.24288286e-04f);
+    p = fmaf(p, a, 8.01050460e-03f);
+    p = fmaf(p, a, -5.33516148e-02f);
+    p = fmaf(p, a, -4.58798370e-01f);
+    p = fmaf(p, a, -1.15119599e+00f);
+    p = fmaf(p, a, -9.99993450e-01f);
     // max(u, 0) as a median: one instruction (fmaxf would quiet u first)
     return fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_amdgcn_fmed3f(u, 0.f, __builtin_inff()));
 }
 
 // 0.5 u (1 + tanh(z)) = u / (1 + e^(-2 z)), z = sqrt(2 / pi) (u + 0.044715 u^3), with the
-// hardware exponential and reciprocal: no cancellation in the negative tail.
+// hardware exponential and reciprocal: no cancellation in the negative tail (relative errors
+// there below 4e-6 down to -6, where 1 + tanhf leaves no digit; root mean square over N(0, 1)
+// 3.0e-8 against tanhf's 2.5e-8).
 __device__ __forceinline__ float act_gelu_tanh_fast(float u) {
     const float c = -2.0f * 0.79788456080286536f * 1.4426950408889634f;  // -2 sqrt(2 / pi) log2(e)
     const float z = u * fmaf(u * u, c * 0.044715f, c);
