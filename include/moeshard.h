@@ -112,8 +112,8 @@ moe_status moe_dispatch(const int32_t *topk_idx, int64_t T, int32_t k, int32_t E
 /* Steps 1 and 2 in one call: moe_route followed by moe_dispatch without x_perm (the grouped
  * rows are read through row_src by moe_expert_ffn_shard_gather / _top1 / _gather_combine),
  * with the same outputs bit for bit.  When one routing workgroup covers the whole batch
- * (decode-sized batches: k <= 8 and T at most 64, or 16 or 32 with many experts in some
- * types) that workgroup also groups the assignments from its picks, in the same launch;
+ * (decode-sized batches: k <= 8 and T at most 64, or 16 or 32 where rows are long or the
+ * experts many) that workgroup also groups the assignments from its picks, in the same launch;
  * otherwise the two steps run as the two calls would.
  *   arguments as moe_route and moe_dispatch (ws: moe_dispatch_workspace_size(T, k, E)
  *   bytes, 16-byte aligned); every argument of both is checked before any launch. */

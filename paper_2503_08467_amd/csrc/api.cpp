@@ -6,6 +6,7 @@
 
 #include "../../include/moeshard.h"
 #include "kernels.h"
+#include "shapes.h"
 
 namespace {
 
@@ -107,7 +108,7 @@ moe_status moe_route_dispatch(const void* x, moe_dtype xdt, int64_t T, int64_t h
     if (sel_bias && (reinterpret_cast<uintptr_t>(sel_bias) & 3u)) return MOE_ERR_INVALID_ARG;
     if (ws_bytes < moe_dispatch_workspace_size(T, k, E)) return MOE_ERR_WORKSPACE;
     const bool bf16 = xdt == MOE_BF16;
-    if (moe::route_dispatch_fusable(bf16, T, static_cast<int>(h), E, k))
+    if (moe::route_groups(bf16, T, static_cast<int>(h), E, k))
         return from_hip(moe::launch_route_dispatch(x, bf16, T, static_cast<int>(h), w_gate, E, k, sel_bias, bias_row_stride,
                                                    renorm, topk_idx, topk_w,
                                                    moe::RouteDispatchOut{counts, offsets, row_src, pos_of}, stream));

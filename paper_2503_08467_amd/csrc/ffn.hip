@@ -34,6 +34,18 @@
 #include <type_traits>
 
 namespace moe {
+
+int device_cus() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+            n = 256;
+        return n;
+    }();
+    return cus;
+}
+
 namespace {
 
 enum Epi { kEpiGelu = 0, kEpiGeluTanh = 1, kEpiSwiglu = 2, kEpiNone = 3 };
@@ -1782,8 +1794,6 @@ int64_t row_tile_bound(int64_t A_max, int E, int bm) {
     return b < A_max ? b : A_max;
 }
 
-int device_cus();
-
 template <int EPI, bool OB>
 hipError_t run_f32_lds(GroupedGemm g, int64_t A_max, hipStream_t s) {
     typedef F32Shape<(EPI == kEpiSwiglu) ? 2 : 1> S;
@@ -1809,17 +1819,6 @@ hipError_t run_f32(GroupedGemm g, int64_t A_max, hipStream_t s) {
     if (blocks == 0) return hipSuccess;
     hipLaunchKernelGGL((gemm_f32<EPI, OB>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, s, g);
     return hipGetLastError();
-}
-
-int device_cus() {
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-            n = 256;
-        return n;
-    }();
-    return cus;
 }
 
 template <int BM, int BW, int BK, int NS, int EPI, bool OB, int WN = 2, bool RM = false>

@@ -7,6 +7,8 @@
 
 namespace moe {
 
+int device_cus();  // CUs of the current device
+
 // Tile constants shared by the packer and the grouped GEMM.
 constexpr int kInnerAlign = 128;  // packed inner width is a multiple of this
 constexpr int kDispatchChunk = 1024;  // assignments per dispatch workgroup
@@ -54,11 +56,7 @@ struct RouteDispatchOut {
     int32_t* pos_of;
 };
 
-// Whether one routing workgroup covers the whole batch, so that it can also group the
-// assignments: k <= 8 and T at most 64 (16 or 32 for the larger E of some types).
-bool route_dispatch_fusable(bool bf16, int64_t T, int h, int E, int k);
-
-// Steps 1 and 2 in one launch (only when route_dispatch_fusable).
+// Steps 1 and 2 in one launch (only when route_groups, see shapes.h).
 hipError_t launch_route_dispatch(const void* x, bool bf16, int64_t T, int h, const void* wg, int E, int k, const float* bias,
                                  int64_t bias_stride, int renorm, int32_t* idx, float* w, RouteDispatchOut out,
                                  hipStream_t s);

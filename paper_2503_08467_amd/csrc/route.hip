@@ -9,6 +9,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "lds_dma.h"
+#include "shapes.h"
 
 #include "../../include/moeshard.h"
 
@@ -301,22 +302,24 @@ struct StridedExperts {
 //
 // RAG: K is not a whole number of steps; the chunks past the end are loaded from the row's last
 // one and replaced by zeros.
+// MT and U (K steps per stage): route_blocks and route_stage.
 template <int NE>
-constexpr int route_waves() { return NE <= 4 ? 8 : 4; }  // (E + 16) MT 16 RW floats of LDS: two workgroups a CU
+constexpr int route_nw() { return NE <= 4 ? 8 : 4; }  // as route_waves; (E + 16) MT 16 RW floats of LDS: two workgroups a CU
 template <int NE>
 constexpr int route_ldw() { return NE * 16 + 4; }  // 16 tokens' 16-byte runs fall on all banks
+// waves per SIMD: two workgroups of eight waves a CU where the stages are short
+template <int NE, int MT>
+constexpr int route_occ() { return (MT == 1 && NE == 1) || (MT == 2 && NE <= 4) ? 4 : NE <= 8 ? 2 : 1; }
 
-template <typename Tin, int NE, int MT, bool RAG>
-__global__ __launch_bounds__(route_waves<NE>() * kWave, MT == 2 && NE <= 4 ? 4 : NE <= 8 ? 2 : 1) void route_kernel(const Tin* __restrict__ x,
+template <typename Tin, int NE, int MT, int U, bool RAG>
+__global__ __launch_bounds__(route_nw<NE>() * kWave, (route_occ<NE, MT>())) void route_kernel(const Tin* __restrict__ x,
                                                                const Tin* __restrict__ wg, int64_t T, int h,
                                                                int E, int k, const float* __restrict__ bias,
                                                                int64_t bias_stride, int renorm,
                                                                int32_t* __restrict__ idx, float* __restrict__ w,
                                                                FusedDispatch fd) {
     constexpr bool kBf = std::is_same<Tin, bf16_t>::value;
-    constexpr int ES = sizeof(Tin), EP = NE * 16, RW = route_waves<NE>(), LDW = route_ldw<NE>(), kTok = 16 * MT;
-    constexpr int kU = (MT == 1 ? 16 : 10) / (NE + MT);
-    constexpr int U = kU > 8 ? 8 : (kU < 1 ? 1 : kU);
+    constexpr int ES = sizeof(Tin), EP = NE * 16, RW = route_nw<NE>(), LDW = route_ldw<NE>(), kTok = 16 * MT;
     constexpr int NV = EP / 8;             // experts per lane in the epilogue
     extern __shared__ __align__(16) float part[];  // [RW][kTok][LDW] partial logits
     const int lane = threadIdx.x & (kWave - 1);
@@ -663,10 +666,10 @@ hipError_t launch_route_lds(const void* x, int64_t T, int h, const void* wg, int
     return launch_route_lds_b<NBW, 1>(x, T, h, wg, E, k, bias, bias_stride, renorm, idx, w, fd, s);
 }
 
-template <typename Tin, int NE, int MT>
+template <typename Tin, int NE, int MT, int U>
 hipError_t launch_route_mt(const void* x, int64_t T, int h, const void* wg, int E, int k, const float* bias,
                            int64_t bias_stride, int renorm, int32_t* idx, float* w, FusedDispatch fd, hipStream_t s) {
-    constexpr int kPart = route_waves<NE>() * 16 * MT * route_ldw<NE>();
+    constexpr int kPart = route_nw<NE>() * 16 * MT * route_ldw<NE>();
     constexpr size_t lds = sizeof(float) * (kPart > kGroupInts ? kPart : kGroupInts);
     static_assert(lds <= 160 * 1024, "LDS per CU");
     const auto go = [&](auto kernel) {
@@ -675,33 +678,45 @@ hipError_t launch_route_mt(const void* x, int64_t T, int h, const void* wg, int 
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
             if (err != hipSuccess) return err;
         }
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(ceil_div(T, 16 * MT))), dim3(route_waves<NE>() * kWave), lds,
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(ceil_div(T, 16 * MT))), dim3(route_nw<NE>() * kWave), lds,
                            s, static_cast<const Tin*>(x), static_cast<const Tin*>(wg), T, h, E, k, bias, bias_stride,
                            renorm, idx, w, fd);
         return hipGetLastError();
     };
-    if (static_cast<int64_t>(h) * sizeof(Tin) % 64 == 0) return go(&route_kernel<Tin, NE, MT, false>);
-    return go(&route_kernel<Tin, NE, MT, true>);
+    if (static_cast<int64_t>(h) * sizeof(Tin) % 64 == 0) return go(&route_kernel<Tin, NE, MT, U, false>);
+    return go(&route_kernel<Tin, NE, MT, U, true>);
 }
 
-// Tokens per workgroup: 16 while that fits the CUs in one round (2500 tokens, 8 experts, h = 4096
-// 10.1 us, 17.4 at 32 tokens) and the gate is small, 32 beyond (8192 tokens, 4 experts, h = 1024 9.7
-// at 16, 7.8 at 32; 30000 tokens, 16 experts, h = 768 37 and 20, 24 at 64) or where re-reading the
-// gate per workgroup costs more (300 tokens, 60 experts 10.4 and 9.7); a batch that one workgroup
-// has to group (fd.counts) takes as many as it holds.  With 32 tokens the stages are shorter, so
-// that two workgroups share a CU (30000 tokens: 24.6 us with one).
+// Every (blocks, steps) that route_blocks and route_stage give for at most 16 NE experts.
 template <typename Tin, int NE>
 hipError_t launch_route_ne(const void* x, int64_t T, int h, const void* wg, int E, int k, const float* bias,
                            int64_t bias_stride, int renorm, int32_t* idx, float* w, FusedDispatch fd, hipStream_t s) {
-#define MOE_ROUTE(MTV) return launch_route_mt<Tin, NE, MTV>(x, T, h, wg, E, k, bias, bias_stride, renorm, idx, w, fd, s)
-    if constexpr (NE <= 4) {
-        if (fd.counts && T > 32) MOE_ROUTE(4);
+    static_assert(NE == 1 || NE == 2 || NE == 4 || NE == 8 || NE == 16, "experts padded to 16 NE");
+    const int mt = route_blocks(T, E, fd.counts != nullptr, device_cus());
+    const int u = route_stage(E, mt, route_run(sizeof(Tin) == 2, h, E));
+#define MOE_ROUTE(MTV, UV) \
+    if (mt == MTV && u == UV) return launch_route_mt<Tin, NE, MTV, UV>(x, T, h, wg, E, k, bias, bias_stride, renorm, idx, w, fd, s)
+    if constexpr (NE == 1) {
+        MOE_ROUTE(1, 4);
+        MOE_ROUTE(1, 6);
+        MOE_ROUTE(2, 2);
+        MOE_ROUTE(2, 3);
+        MOE_ROUTE(4, 2);
+    } else if constexpr (NE == 2) {
+        MOE_ROUTE(1, 2);
+        MOE_ROUTE(1, 5);
+        MOE_ROUTE(2, 1);
+        MOE_ROUTE(4, 1);
+    } else if constexpr (NE == 4) {
+        MOE_ROUTE(1, 3);
+        MOE_ROUTE(2, 1);
+        MOE_ROUTE(4, 1);
+    } else {
+        MOE_ROUTE(1, 1);
+        MOE_ROUTE(2, 1);
     }
-    if constexpr (NE <= 8) {
-        if (T > 16 && (fd.counts || NE > 2 || T > 16 * 256)) MOE_ROUTE(2);
-    }
-    MOE_ROUTE(1);
 #undef MOE_ROUTE
+    return hipErrorInvalidValue;
 }
 
 template <typename Tin>
@@ -715,11 +730,6 @@ hipError_t launch_route_t(const void* x, int64_t T, int h, const void* wg, int E
 }
 
 }  // namespace
-
-// Streaming the chunks through LDS pays where the gate is large: 64 experts, 32768 tokens 20.4 us
-// against 44.5 for route_kernel, 128 experts, 30000 tokens 23.5 against 39.8, 64 tokens 9.6
-// against 14.4.
-static bool route_in_lds(bool bf16, int h, int E) { return bf16 && h % kRK == 0 && E > 32; }
 
 static hipError_t route_any(const void* x, bool bf16, int64_t T, int h, const void* wg, int E, int k,
                             const float* bias, int64_t bias_stride, int renorm, int32_t* idx, float* w,
@@ -738,14 +748,6 @@ hipError_t launch_route(const void* x, bool bf16, int64_t T, int h, const void* 
                         const float* bias, int64_t bias_stride, int renorm, int32_t* idx, float* w,
                         hipStream_t s) {
     return route_any(x, bf16, T, h, wg, E, k, bias, bias_stride, renorm, idx, w, FusedDispatch{}, s);
-}
-
-bool route_dispatch_fusable(bool bf16, int64_t T, int h, int E, int k) {
-    if (T < 1 || k > kRegPicks) return false;
-    if (route_in_lds(bf16, h, E) || E <= 32) return T <= 64;
-    // one workgroup's fp32 matrix rate: 20 tokens, 60 experts, h = 2048 take 34 us in one, 27 in two
-    if (!bf16 || E > 128) return T <= 16;
-    return T <= (E <= 64 ? 64 : 32);
 }
 
 hipError_t launch_route_dispatch(const void* x, bool bf16, int64_t T, int h, const void* wg, int E, int k, const float* bias,

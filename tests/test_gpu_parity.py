@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 import synth
+from _shapes import ROUTE_FORMS
 from _util import by_expert, compare_routing, normwise, rowwise, to_dev
 
 torch = pytest.importorskip("torch")
@@ -82,12 +83,12 @@ def test_route_shapes_and_bias(dtype, T, h, E, k, bias_kind):
 
 @pytest.mark.parametrize("T,h,E,k", [(1, 128, 40, 1), (17, 256, 64, 2), (64, 1024, 64, 2), (64, 128, 128, 8),
                                      (33, 64, 256, 5), (50, 192, 100, 3),
-                                     (65, 128, 64, 2), (64, 128, 64, 9), (40, 128, 32, 2)])  # separate launches
+                                     (40, 128, 32, 2),                       # 32 experts: the other kernel
+                                     (65, 128, 64, 2), (64, 128, 64, 9), (40, 1024, 32, 2)])  # separate launches
 @pytest.mark.parametrize("bias_kind", ["none", "row", "shared"])
 def test_route_dispatch_matches_two_calls(T, h, E, k, bias_kind):
     """moe_route_dispatch = moe_route + moe_dispatch (indices only), every output bit for bit:
-    one launch when a single workgroup routes the batch (T <= 64, k <= 8, 32 < E), the two
-    launches otherwise."""
+    one launch when a single workgroup routes the batch, the two launches otherwise."""
     rng = np.random.default_rng(T * 1000 + E + k)
     x = synth.round_to_bf16(rng.standard_normal((T, h)).astype(np.float32))
     wg = synth.round_to_bf16((rng.standard_normal((E, h)) * 0.05).astype(np.float32))
@@ -134,6 +135,29 @@ def test_route_and_grouping_in_one_call(dtype, T, h, E, k):
     assert torch.equal(i1, i2) and torch.equal(w1, w2)
     for key in ("counts", "offsets", "pos_of", "row_src"):
         assert torch.equal(getattr(d1, key), getattr(d2, key)), key
+
+
+@pytest.mark.parametrize("dtype,T,h,E,k,form", ROUTE_FORMS)
+def test_route_forms(dtype, T, h, E, k, form):
+    """Every form of the routing launch (blocks of tokens per workgroup, K steps per stage): the
+    picks against the oracle, and every output bit for bit that of the same tokens routed 16 at
+    a time (one block, the same order of K)."""
+    rng = np.random.default_rng(T + 31 * h + E)
+    x = rng.standard_normal((T, h)).astype(np.float32)
+    wg = (rng.standard_normal((E, h)) * 0.05).astype(np.float32)
+    if dtype == "bf16":
+        x, wg = synth.round_to_bf16(x), synth.round_to_bf16(wg)
+    bias = rng.standard_normal((T, E)).astype(np.float32)
+    xd, wd, bd = to_dev(x, tdt(dtype)), to_dev(wg, tdt(dtype)), to_dev(bias, torch.float32)
+    _check_route(x, wg, bias, k, k > 1, dtype, False)
+    idx, w, d = moe.route_dispatch(xd, wd, k, bd, k > 1)
+    for t in (0, 16, T // 32 * 16, max(0, T - 16)):
+        s = slice(t, min(t + 16, T))
+        i1, w1 = moe.route(xd[s].contiguous(), wd, k, bd[s].contiguous(), k > 1)
+        assert torch.equal(i1, idx[s]) and torch.equal(w1.view(torch.int32), w[s].view(torch.int32))
+    d1 = moe.dispatch(idx, xd, E, x_perm=False)
+    for key in ("counts", "offsets", "pos_of", "row_src"):
+        assert torch.equal(getattr(d1, key), getattr(d, key)), key
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])

@@ -1,0 +1,38 @@
+"""The dispatch rules by themselves (CPU): the GPU tests' cases reach the forms that they name, and
+no sizes ask for a form that is not compiled."""
+import itertools
+
+from _shapes import CUS, ROUTE_FORMS, ask
+
+
+def _route(dtype, T, h, E, k, want=1):
+    return f"route {int(dtype == 'bf16')} {T} {h} {E} {k} {want} {CUS}"
+
+
+def test_route_cases_reach_their_forms():
+    got = ask([_route(*c[:5]) for c in ROUTE_FORMS])
+    assert got == [c[5] for c in ROUTE_FORMS]
+
+
+def test_every_route_form_is_compiled():
+    # (blocks, steps) per number of experts, as route.hip compiles them
+    built = {16: {"1 x 4", "1 x 6", "2 x 2", "2 x 3", "4 x 2"}, 32: {"1 x 2", "1 x 5", "2 x 1", "4 x 1"}, 64: {"1 x 3", "2 x 1", "4 x 1"},
+             128: {"1 x 1", "2 x 1"}, 256: {"1 x 1", "2 x 1"}}
+    sizes = list(itertools.product(("bf16", "f32"), (1, 16, 17, 32, 33, 64, 65, 4096, 4097, 16383, 16384, 100000),
+                                   (8, 64, 256, 328, 512, 768, 1024, 1032, 2048, 4096), (1, 16, 17, 32, 33, 64, 65, 128, 129, 256),
+                                   (1, 8, 9), (0, 1)))
+    got = ask([_route(d, T, h, E, min(k, E), want) for d, T, h, E, k, want in sizes])
+    for (d, T, h, E, k, want), form in zip(sizes, got):
+        if form.startswith("lds"):
+            continue
+        n = next(v for v in built if E <= v)
+        assert form.removesuffix(" grouped") in built[n], (d, T, h, E, k, want, form)
+        if form.endswith(" grouped"):
+            assert T <= 16 * int(form.split()[0]) and min(k, E) <= 8 and want
+
+
+def test_the_kernel_of_a_token_does_not_depend_on_its_batch():
+    # the two routing kernels sum K in different orders: which one is a matter of type, h and E
+    for d, h, E in itertools.product(("bf16", "f32"), (64, 72, 4096), (1, 24, 32, 33, 64, 256)):
+        got = ask([_route(d, T, h, E, 1) for T in (1, 16, 17, 64, 65, 8192, 100000)])
+        assert len({g.startswith("lds") for g in got}) == 1
