@@ -45,7 +45,7 @@ PEAK_HBM_GBS = 8000.0
 PEAK_BF16_TFLOPS = 2500.0
 PEAK_F32_TFLOPS = 157.3
 FFN_SOURCES = ["paper_2503_08467_amd/csrc/ffn.hip", "paper_2503_08467_amd/csrc/common.h",
-               "paper_2503_08467_amd/csrc/lds_dma.h", "paper_2503_08467_amd/csrc/kernels.h"]
+               "paper_2503_08467_amd/csrc/lds_dma.h", "paper_2503_08467_amd/csrc/kernels.h", "paper_2503_08467_amd/csrc/shapes.h"]
 
 
 def ffn_source_hash() -> str:

@@ -10,8 +10,8 @@
 // the host-known bound A_max, at most as many workgroups per CU as LDS allows, a multiple
 // of the 8 XCDs), so the counts are never read back to the host.
 //
-// bf16, many rows per expert (gemm_bf16_lds, gemm_up_pairs, gemm_turns): 128- or 256-row
-// tiles, v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  Weights and H are stored K-blocked
+// bf16, many rows per expert (gemm_bf16_lds, gemm_up_pairs, gemm_turns): tiles of 64 to 256
+// rows, v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  Weights and H are stored K-blocked
 // (blocks of 32 K values, all rows side by side), so every stage of 32 K values of a run of
 // rows is one contiguous stretch that 1 KiB direct-to-LDS loads fetch; stages stay in flight
 // across K steps and tiles.  The epilogue applies the activation in fp32, rounds once, and
@@ -26,6 +26,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "lds_dma.h"
+#include "shapes.h"
 
 #include "../../include/moeshard.h"
 
@@ -68,9 +69,9 @@ struct GroupedGemm {
     const int32_t* scatter;
     const float* scatter_w;
     int64_t c_rows;
-    // Down-projection only: partial sums in fp32 to partial[s][row][N] (no scale, no scatter)
-    // for a kernel that adds the parts in order.  gemm_f32_lds: with ksplit > 1 every tile as
-    // ksplit parts of K / ksplit each.  gemm_stream: whole sums, one part.
+    // Down-projection only: sums in fp32 to partial[s][row][N] (no scale, no scatter) for a
+    // kernel that adds the parts in order.  gemm_f32_lds: with ksplit > 1 every tile as ksplit
+    // parts of K / ksplit each.  gemm_stream: whole sums, one part.
     int ksplit;
     float* partial;
 };
@@ -487,21 +488,18 @@ void gemm_bf16_lds(GroupedGemm g) {
 
     // Per-lane byte offsets of this wave's loads: load j fills LDS rows (NW j + wave) * RPI
     // + lane / CPR of a stage, slot lane % CPR, with global chunk slot ^ swz(row).  Rows past
-    // a buffer smaller than one tile repeat its last row.
+    // a buffer smaller than one tile repeat its last row.  The weights' are the same for every
+    // tile, the activations' (j < kAJ) are set with it.
     uint32_t voff[LPW];
     {
         const int r_lane = lane / CPR, c_lane = lane % CPR;
-        const int a_lim = static_cast<int>(g.rows_max < BM ? g.rows_max : BM) - 1;
         const int b_lim = (g.N < BN ? g.N : BN) - 1;
 #pragma unroll
-        for (int j = 0; j < LPW; ++j) {
+        for (int j = kAJ; j < LPW; ++j) {
             const int R = (j * NW + wave) * RPI + r_lane;
             const int kc = c_lane ^ ((R >> SH) & (CPR - 1));
-            int r;
-            if (j < kAJ) r = min(R, a_lim);
-            else r = min((R - BM) % BN, b_lim);
-            const uint32_t row_bytes = (RM || (j < kAJ && kUp)) ? static_cast<uint32_t>(2 * g.K) : 64u;
-            voff[j] = static_cast<uint32_t>(r) * row_bytes + static_cast<uint32_t>(kc * 16);
+            const uint32_t row_bytes = RM ? static_cast<uint32_t>(2 * g.K) : 64u;
+            voff[j] = static_cast<uint32_t>(min((R - BM) % BN, b_lim)) * row_bytes + static_cast<uint32_t>(kc * 16);
         }
     }
 
@@ -899,7 +897,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_up_pairs(GroupedGemm g) {
 
 // ------------------------------------------------------------------ bf16 MFMA kernel, two wave groups in turn
 //
-// For calls whose experts have many rows (which calls: turns_up, turns_down below), where the
+// For calls whose experts have many rows (which calls: turns_up, turns_down in shapes.h), where the
 // matrix cores are the bound.  256 x 256 tiles (SwiGLU: 128 columns of W1 and the same of W3),
 // eight waves in one workgroup per CU: per product two thirds of the LDS fills (and so of the
 // L2 reads) of the 128 x 256 tiles above.  K advances 32 at a time through a ring of four
@@ -1473,7 +1471,7 @@ __global__ __launch_bounds__(kThreads, (F32Shape<(EPI == kEpiSwiglu) ? 2 : 1>::k
 
 // ------------------------------------------------------------------ few rows per expert: weights streamed into registers
 //
-// For calls whose experts have few rows (which calls: stream_rows below), where reading the
+// For calls whose experts have few rows (which calls: stream_rows in shapes.h), where reading the
 // weights is all the time there is.  A workgroup owns NC weight rows (SwiGLU: NC / 2 of each
 // matrix) and a tile of at most 16 MR activation rows of one expert; its NW waves cut K
 // between them, so that even one expert's matrix keeps hundreds of waves loading.  A wave
@@ -1669,8 +1667,8 @@ __global__ __launch_bounds__(512, MR == 1 ? 4 : 2) void gemm_stream(GroupedGemm 
 // out[p] = sum over s of partial[s][p] (s ascending) for the grouped rows p of the call,
 // [offsets[0], offsets[E]); with scatter (top-1), out[t] = w[t] * that sum for
 // t = scatter[p] instead (the down-projection's own epilogue, applied after the parts
-// meet).  N % 4 == 0.  S (2, 4 or 8 parts) is a template argument so that a thread's S
-// loads are issued together (one memory round trip) before the sum.
+// meet).  N % 4 == 0.  S (four parts) is a template argument so that a thread's S loads are
+// issued together (one memory round trip) before the sum.
 
 template <bool OB, int S>
 __global__ __launch_bounds__(256) void split_reduce(const float* __restrict__ partial, int64_t rows_max,
@@ -1720,10 +1718,10 @@ __global__ __launch_bounds__(256) void split_reduce(const float* __restrict__ pa
 }
 
 
-// Steps 4 and 5 together when the second product's K is split: for token t and 8 columns,
+// Steps 4 and 5 together for decode-sized calls (hands_over_sums): for token t and 8 columns,
 //     y[t] = sum over picks j of w[t, j] * round_ydt(sum over s of partial[s][pos_of[t, j]])
-// -- exactly split_reduce's sum (parts in order), rounded to y_perm's type as split_reduce
-// stores it, then combine's weighted sum (fp32, pick order, invalid picks skipped) rounded
+// -- the second product's S parts in order (one where its sums are whole), rounded to y_perm's
+// type as the product or split_reduce stores it, then combine's weighted sum (fp32, pick order, invalid picks skipped) rounded
 // once: the same bits as the two launches, without writing or reading y_perm.
 template <bool YB, bool OB, int S>
 __global__ __launch_bounds__(256) void split_combine(const float* __restrict__ partial, int64_t rows_max,
@@ -1789,11 +1787,6 @@ __global__ __launch_bounds__(256) void split_combine(const float* __restrict__ p
 
 // ------------------------------------------------------------------ launch
 
-int64_t row_tile_bound(int64_t A_max, int E, int bm) {
-    const int64_t b = ceil_div(A_max, bm) + E;
-    return b < A_max ? b : A_max;
-}
-
 template <int EPI, bool OB>
 hipError_t run_f32_lds(GroupedGemm g, int64_t A_max, hipStream_t s) {
     typedef F32Shape<(EPI == kEpiSwiglu) ? 2 : 1> S;
@@ -1840,37 +1833,6 @@ hipError_t run_bf16_lds(GroupedGemm g, int64_t A_max, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Tile shape: 128 activation rows x 256 weight rows, 32-wide K steps, three stages (two in
-// flight) in 72 KiB of LDS, so that two workgroups share a CU and one's epilogue and
-// pipeline fill overlap the other's MFMAs.
-//
-// The up-projection's weights are K-blocked when h % 32 == 0; otherwise they are row-major and
-// the kernel's RM form reads them (1531 tokens, 24 experts, h = 776, f = 1365: 34.5 us,
-// 49.7 through a register-staged kernel).  The
-// down-projection's K is fp, always a multiple of 128.
-//
-// Few tiles leave CUs idle and few bytes in flight, so such calls take smaller ones.  Measured
-// (us, up / down; each output element's K sum is the same in any shape):
-// - experts that average at most 48 rows, 64 x 256: 64 experts (1024 x 1024) 2000 rows 34 / 35
-//   -> 30 / 30, 3000 rows 42 / 42 -> 38 / 37; 4000 rows would lose (35 / 32 -> 40 / 39);
-// - at most 5/8 of a 128 x 256 tile per CU, 128 x 128 in four stages, three workgroups a CU: 16
-//   experts (1408 x 1024) 2000 rows 34 / 27 -> 25 / 19; 8 experts (3072 x 384 SwiGLU) 4000 rows up
-//   65 -> 39; 24 experts (776 x 1365) 3062 rows down 33 -> 22; at 3/4 of a tile 31 -> 34, 25 -> 28;
-// - at most 1/4, 64 x 128 for the up-projection: 4 experts (1728 x 1520) 823 rows 40 -> 18 (24 at
-//   128 x 128).
-// When the down-projection's tiles fit on the CUs in one round even 384 columns wide, and those
-// waste no more columns than 256-wide ones, it runs 128 x 384 tiles, one workgroup per CU with
-// 96 KiB of stages: every tile then streams its weights with more bytes in flight instead of a
-// third of the CUs taking a second tile (64 experts, 3072 x 768, 8192 rows 108 -> 89; 1024 columns
-// in three would lose: 26 -> 30).  That workgroup has 8 waves (2 x 4, each 64 x 96), two per SIMD, so
-// that one wave's LDS reads, loads and barrier waits overlap the other's MFMAs.
-bool thin_experts(int64_t A_max, int E) { return A_max <= 48 * static_cast<int64_t>(E); }
-
-// Tiles of 128 rows with half an empty row tile per expert.
-double expected_tiles(int64_t A_max, int E, int64_t n_tiles) {
-    return (static_cast<double>(A_max) / 128 + 0.5 * E) * static_cast<double>(n_tiles);
-}
-
 template <int EPI>
 hipError_t run_up_pairs(GroupedGemm g, int64_t A_max, hipStream_t s) {
     static const hipError_t attr =
@@ -1884,23 +1846,6 @@ hipError_t run_up_pairs(GroupedGemm g, int64_t A_max, hipStream_t s) {
     hipLaunchKernelGGL((gemm_up_pairs<EPI>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), kUpPairBytes, s,
                        g);
     return hipGetLastError();
-}
-
-// Which launches take gemm_turns, from the sizes the host knows.  Measured over A = 3000 ..
-// 65536 rows, 8 .. 64 experts, K = 512 .. 4096 (us, the 128 x 256 tiles against 256 x 256):
-// down-projection: K = 4096 545 / 491 (1024 rows per expert), 302 / 288 (512), 213 / 210 (256);
-//   K = 2816 67 / 64 (188); K = 1792 140 / 138; but K = 1024 28 / 27 (128), K = 512 37 / 44 (512):
-//   a short K loop does not pay for its fill and the single workgroup's exposed epilogue;
-// up-projection: K = 4096 941 / 799, 369 / 307, 262 / 219 and, in less than one round of tiles,
-//   141 / 124, but 137 / 173 where the tiles are just over one round of the CUs; K = 2048
-//   419 / 378 over many rounds, a tie below; K = 1024 702 / 708.
-bool turns_rows(int64_t A_max, int E) { return A_max >= 192 * static_cast<int64_t>(E); }
-bool turns_down(const GroupedGemm& g, int64_t A_max) { return g.K >= 1536 && turns_rows(A_max, g.E); }
-bool turns_up(const GroupedGemm& g, int64_t A_max, int n_tiles) {
-    if (g.K % 32 != 0 || g.K < 1536 || !turns_rows(A_max, g.E)) return false;
-    // expected rounds of tiles: half an empty row tile per expert
-    const double rounds = (static_cast<double>(A_max) / 256 + 0.5 * g.E) * n_tiles / device_cus();
-    return rounds >= 4 || (g.K >= 3072 && (rounds >= 1.6 || (rounds <= 1 && rounds >= 0.75)));
 }
 
 template <int EPI, bool OB>
@@ -1917,37 +1862,21 @@ hipError_t run_turns(GroupedGemm g, int64_t A_max, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Which calls stream their weights (gemm_stream), from the call's row bound and its number of
-// experts: the same answer for every launch path of a call, since the waves' K parts make its
-// sums round differently.  Measured (us, up / down (+ split sum), tiled kernels against this):
-// bf16: 1 expert 16 rows (2048 x 2048) 20 / 7 + 3 against 7 / 6, 4 experts 128 rows 22 / 11 + 4
-//   against 13 / 11, 250 rows 47 / 14 + 5 against 20 / 16; 8 experts (3072 x 1536 SwiGLU) 500
-//   rows 61 / 28 + 6 against 58 / 28 + 5; 64 experts (1024 x 4096) 1000 rows 110 / 109 against
-//   110 / 101, but 2000 rows 107 / 111 against 139 / 117; 128 experts (768 x 768) 250 rows 25 / 14
-//   + 4 against 12 / 10, 1000 rows 27 / 24 against 27 / 26;
-// fp32: 8 experts (768 x 3072) 4 rows 22 / 19 + 4 against 11 / 11, 64 rows 29 / 27 + 5 against
-//   26 / 28, 128 rows 29 / 27 + 4 against 33 / 41 (its matrix rate is a sixteenth of bf16's);
-//   only where the tiled kernel's up-projection has at most one 128-column tile per CU: with
-//   more, its 128-byte pieces of a row stream the weights faster (layers of 24 experts 3456 x 488
-//   167 -> 136, 64 experts 2624 x 168 203 -> 173, but 96 experts 832 x 1216 112 -> 136, 64 experts
-//   640 x 2564 209 -> 253).
-bool stream_rows(int64_t rows_max, int E, int64_t fp, bool bf16) {
-    if (bf16) return rows_max <= 512 || rows_max <= 16 * static_cast<int64_t>(E);
-    return (rows_max <= 64 || rows_max <= 8 * static_cast<int64_t>(E)) &&
-           std::min<int64_t>(rows_max, E) * (fp / 128) <= device_cus();
-}
-
 template <typename T, int EPI, bool OB, int NC, int MR>
 hipError_t run_stream_t(GroupedGemm g, int64_t A_max, hipStream_t s) {
     g.n_tiles = static_cast<int>(ceil_div(g.N, EPI == kEpiSwiglu ? NC / 2 : NC));
     const int64_t items = row_tile_bound(A_max, g.E, 16 * MR) * g.n_tiles;
     if (items == 0) return hipSuccess;
     const dim3 grid(static_cast<unsigned>(round_up(items, 8)));
-    if (static_cast<int64_t>(g.K) * sizeof(T) % 64 == 0)
+    if (static_cast<int64_t>(g.K) * sizeof(T) % 64 == 0) {
         hipLaunchKernelGGL((gemm_stream<T, EPI, OB, NC, MR, false>), grid, dim3(512), 0, s, g);
-    else
+        return hipGetLastError();
+    }
+    if constexpr (EPI != kEpiNone) {  // the down-projection's K is a multiple of 128
         hipLaunchKernelGGL((gemm_stream<T, EPI, OB, NC, MR, true>), grid, dim3(512), 0, s, g);
-    return hipGetLastError();
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 // Weight rows per workgroup: as many of 64, 32, 16 as still give every CU two workgroups (one
@@ -1974,36 +1903,28 @@ hipError_t run_stream(GroupedGemm g, int64_t A_max, hipStream_t s) {
 
 template <int EPI, bool OB>
 hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
-    constexpr bool kUp = EPI != kEpiNone;
-    if constexpr (kUp) {
-        if (turns_up(g, A_max, static_cast<int>(ceil_div(g.N, EPI == kEpiSwiglu ? 128 : 256))))
-            return run_turns<EPI, OB>(g, A_max, s);
-        if (g.K % 32 == 0) {
-            if (thin_experts(A_max, g.E)) return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
-            const double tiles = expected_tiles(A_max, g.E, ceil_div(g.N, EPI == kEpiSwiglu ? 128 : 256));
-            if (4 * tiles <= device_cus()) return run_bf16_lds<64, 128, 32, 3, EPI, OB>(g, A_max, s);
-            if (8 * tiles <= 5 * device_cus()) return run_bf16_lds<128, 128, 32, 4, EPI, OB>(g, A_max, s);
+    if constexpr (EPI != kEpiNone) {
+        static_assert(OB, "H is bf16");
+        switch (up_shape(A_max, g.E, g.K, g.N, EPI == kEpiSwiglu, device_cus())) {
+            case kTurns256x256: return run_turns<EPI, OB>(g, A_max, s);
+            case kTile64x256: return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
+            case kTile64x128: return run_bf16_lds<64, 128, 32, 3, EPI, OB>(g, A_max, s);
+            case kTile128x128: return run_bf16_lds<128, 128, 32, 4, EPI, OB>(g, A_max, s);
+            case kPairs128x256: return run_up_pairs<EPI>(g, A_max, s);
+            case kTile128x256: return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);
+            case kRows128x256: return run_bf16_lds<128, 256, 32, 3, EPI, OB, 2, true>(g, A_max, s);
+            default: return hipErrorInvalidValue;
         }
-        // activation rows in 128-byte pieces when K allows it (see gemm_up_pairs)
-        if constexpr (OB) {
-            if (g.K % 64 == 0) return run_up_pairs<EPI>(g, A_max, s);
-        }
-        if (g.K % 32 == 0) return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);
-        return run_bf16_lds<128, 256, 32, 3, EPI, OB, 2, true>(g, A_max, s);
     } else {
         if (g.K % 32 != 0) return hipErrorInvalidValue;  // not reachable through the C ABI (fp % 128 == 0)
-        const bool fits_384 = ceil_div(g.N, 384) * 384 <= ceil_div(g.N, 256) * 256 &&
-                              row_tile_bound(A_max, g.E, 128) * ceil_div(g.N, 384) <= device_cus();
-        // 32 experts (1568 x 640), 9542 rows: the layer 101 us at 384 columns, 105 in turns; from
-        // 375 rows per expert turns win there too (48.6 -> 45.2)
-        if (turns_down(g, A_max) && !(fits_384 && A_max < 320 * static_cast<int64_t>(g.E)))
-            return run_turns<EPI, OB>(g, A_max, s);
-        if (thin_experts(A_max, g.E)) return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
-        if (8 * expected_tiles(A_max, g.E, ceil_div(g.N, 256)) <= 5 * device_cus())
-            return run_bf16_lds<128, 128, 32, 4, EPI, OB>(g, A_max, s);
-        if (fits_384)
-            return run_bf16_lds<128, 384, 32, 3, EPI, OB, 4>(g, A_max, s);
-        return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);
+        switch (down_shape(A_max, g.E, g.K, g.N, device_cus())) {
+            case kTurns256x256: return run_turns<EPI, OB>(g, A_max, s);
+            case kTile64x256: return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
+            case kTile128x128: return run_bf16_lds<128, 128, 32, 4, EPI, OB>(g, A_max, s);
+            case kTile128x384: return run_bf16_lds<128, 384, 32, 3, EPI, OB, 4>(g, A_max, s);
+            case kTile128x256: return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);
+            default: return hipErrorInvalidValue;
+        }
     }
 }
 
@@ -2015,8 +1936,8 @@ hipError_t gemm1(bool bf16, bool stream, GroupedGemm g, int64_t A_max, hipStream
 
 // Both matmuls of the expert step.  grid_rows sizes the launches (an upper bound of the
 // rows the offsets describe); rows_max is the row count of x_perm, H and y_perm.
-// Step 5 folded into the expert step (CombineArgs given and the second product split): the
-// parts' sum goes straight into y through split_combine instead of into y_perm.
+// Step 5 folded into the expert step (CombineArgs given, a call that hands_over_sums): the second
+// product's fp32 sums go straight into y through split_combine instead of into y_perm.
 struct CombineArgs {
     const int32_t* pos_of;
     const float* w;
@@ -2038,7 +1959,7 @@ hipError_t launch_split_reduce_t(const float* partial, int64_t rows_max, int h, 
     return hipGetLastError();
 }
 
-// four parts: the fp32 down-projection's (down_ksplit)
+// four parts: the fp32 down-projection's (down_parts)
 hipError_t launch_split_reduce(bool ob, const float* partial, int64_t rows_max, int h, int64_t grid_rows,
                                const int32_t* offsets, int E, void* out, const int32_t* scatter,
                                const float* scatter_w, int64_t c_rows, hipStream_t s) {
@@ -2076,7 +1997,7 @@ hipError_t ffn_pair(const void* x_perm, const int32_t* offsets, int64_t grid_row
                     int call_E = 0) {
     if (grid_rows == 0) return hipSuccess;
     // call_E: the call's experts where this launch covers one of them
-    const bool stream = stream_rows(rows_max, call_E ? call_E : E, fp, bf16);
+    const bool stream = stream_rows(rows_max, call_E ? call_E : E, fp, bf16, device_cus());
     GroupedGemm g1{};
     g1.a = x_perm;
     g1.gather = gather;
@@ -2114,31 +2035,30 @@ hipError_t ffn_pair(const void* x_perm, const int32_t* offsets, int64_t grid_row
         g2.scatter_w = scatter_w;
         g2.c_rows = a_rows;
     }
-    // fp32 sums after H in the workspace: ksplit x rows_max x h
+    // fp32 sums after H in the workspace: parts x rows_max x h
     float* const partial = reinterpret_cast<float*>(static_cast<unsigned char*>(hbuf) +
                                                     round_up(rows_max * fp * (bf16 ? 2 : 4), 256));
+    // the parts are chosen from rows_max (the call's row bound), so a per-expert launch of this
+    // call splits like the grouped one
+    const int parts = down_parts(rows_max, fp, bf16, stream);
+    if (comb || parts > 1) {
+        g2.ksplit = parts;
+        g2.partial = partial;
+        if (bf16 && !stream) g2.c = partial;  // whole sums as the tiled kernels' fp32 output
+        if (stream) err = bf16 ? run_stream<bf16_t, kEpiNone, false>(g2, grid_rows, s) : run_stream<float, kEpiNone, false>(g2, grid_rows, s);
+        else err = bf16 ? run_bf16_best<kEpiNone, false>(g2, grid_rows, s) : run_f32<kEpiNone, false>(g2, grid_rows, s);
+        if (err != hipSuccess) return err;
+        if (!comb)
+            return launch_split_reduce(y_bf16, partial, rows_max, h, grid_rows, offsets, E, y_perm, g2.scatter,
+                                       g2.scatter_w, g2.c_rows, s);
+        return comb->T == 0 ? hipSuccess : launch_split_combine(y_bf16, parts, partial, rows_max, h, *comb, s);
+    }
     if (stream) {
-        // whole sums: straight into y_perm, or for split_combine as one part
-        if (comb) g2.partial = partial;
-        if (bf16) err = y_bf16 ? run_stream<bf16_t, kEpiNone, true>(g2, grid_rows, s) : run_stream<bf16_t, kEpiNone, false>(g2, grid_rows, s);
-        else err = y_bf16 ? run_stream<float, kEpiNone, true>(g2, grid_rows, s) : run_stream<float, kEpiNone, false>(g2, grid_rows, s);
-        if (err != hipSuccess || !comb || comb->T == 0) return err;
-        return launch_split_combine(y_bf16, 1, partial, rows_max, h, *comb, s);
+        if (bf16) return y_bf16 ? run_stream<bf16_t, kEpiNone, true>(g2, grid_rows, s) : run_stream<bf16_t, kEpiNone, false>(g2, grid_rows, s);
+        return y_bf16 ? run_stream<float, kEpiNone, true>(g2, grid_rows, s) : run_stream<float, kEpiNone, false>(g2, grid_rows, s);
     }
     if (bf16) return y_bf16 ? run_bf16_best<kEpiNone, true>(g2, grid_rows, s) : run_bf16_best<kEpiNone, false>(g2, grid_rows, s);
-    // the split is chosen from rows_max (the call's row bound), so a per-expert launch of
-    // this call splits like the grouped one
-    g2.ksplit = down_ksplit(rows_max, fp, false);
-    if (g2.ksplit <= 1) return y_bf16 ? run_f32<kEpiNone, true>(g2, grid_rows, s) : run_f32<kEpiNone, false>(g2, grid_rows, s);
-    g2.partial = partial;
-    err = run_f32<kEpiNone, false>(g2, grid_rows, s);  // partial tiles only
-    if (err != hipSuccess) return err;
-    if (comb) {
-        if (comb->T == 0) return hipSuccess;
-        return launch_split_combine(y_bf16, g2.ksplit, partial, rows_max, h, *comb, s);
-    }
-    return launch_split_reduce(y_bf16, partial, rows_max, h, grid_rows, offsets, E, y_perm, g2.scatter, g2.scatter_w,
-                               g2.c_rows, s);
+    return y_bf16 ? run_f32<kEpiNone, true>(g2, grid_rows, s) : run_f32<kEpiNone, false>(g2, grid_rows, s);
 }
 
 }  // namespace
@@ -2161,9 +2081,9 @@ hipError_t launch_ffn_gather_combine(const void* x, int64_t T, const int32_t* ro
                                      const float* topk_w, void* y, bool out_bf16, void* hbuf, hipStream_t s,
                                      bool* y_perm_written) {
     const int64_t A_max = T * k;
-    const bool split = down_ksplit(A_max, fp, bf16) > 1;
-    *y_perm_written = !split;
-    if (split) {
+    const bool sums = hands_over_sums(A_max, fp, bf16);
+    *y_perm_written = !sums;
+    if (sums) {
         const CombineArgs comb{pos_of, topk_w, T, k, y, out_bf16};
         return ffn_pair(x, offsets, A_max, A_max, E, h, fp, act, bf16, w1t, w3t, w2t, y_perm, y_bf16, hbuf, s,
                         row_src, T, nullptr, &comb);

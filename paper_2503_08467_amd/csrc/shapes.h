@@ -3,6 +3,7 @@
 // figures beside the rules were measured at 256.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -73,6 +74,142 @@ inline int route_stage(int E, int blocks, int run) {
     if (E <= 16) return blocks == 1 ? pick(4, 6) : blocks == 2 ? pick(2, 3) : 2;
     if (E <= 32) return blocks > 1 ? 1 : run == 5 ? 5 : 2;
     return E <= 64 && blocks == 1 ? 3 : 1;
+}
+
+// ---- Step 4
+//
+// A: the call's row bound; E: the experts of the launch; K, N: the product's sizes.
+
+inline int64_t tiles_of(int64_t n, int64_t d) { return (n + d - 1) / d; }
+
+// Row tiles of bm rows that A rows of E experts can have at most.
+inline int64_t row_tile_bound(int64_t A, int E, int bm) { return std::min<int64_t>(tiles_of(A, bm) + E, A); }
+
+// Decode-sized calls, whose second product stays in fp32 sums that the combine reads
+// (moe_expert_ffn_shard_gather_combine): at most 512 bf16 or 1024 fp32 rows, and a packed inner
+// width fp (a multiple of 128) of at least 512 or 1024.
+inline bool hands_over_sums(int64_t A, int64_t fp, bool bf16) {
+    return bf16 ? A <= 512 && fp >= 512 : A <= 1024 && fp >= 1024;
+}
+
+// K parts of the second product: four where its fp32 form does not stream and hands_over_sums, so
+// that few row tiles with a long K loop each spread their weight reads over more workgroups; else
+// whole sums.
+inline int down_parts(int64_t A, int64_t fp, bool bf16, bool stream) {
+    return !bf16 && !stream && hands_over_sums(A, fp, bf16) ? 4 : 1;
+}
+
+// Bytes of fp32 sums that the workspace reserves past H for a bound of A rows: 4 x rows x h floats
+// of fp32 calls (down_parts), up to 8 x 256 of bf16 ones (an earlier form split their K; the size is
+// part of the ABI).  The most that any call with at most A rows has, so that a workspace sized for a
+// bound also serves every smaller call.
+inline size_t down_partial_bytes(int64_t A, int64_t h, int64_t fp, bool bf16) {
+    const auto parts = [&](int64_t a) -> int64_t {
+        if (!hands_over_sums(a, fp, bf16)) return 0;
+        return !bf16 ? 4 : std::min<int64_t>(a <= 256 ? 8 : 4, fp >= 2048 && fp % 256 == 0 ? 8 : fp >= 1024 ? 4 : 2);
+    };
+    int64_t most = 0;
+    for (int64_t end : {int64_t(256), int64_t(512), int64_t(1024)})
+        most = std::max(most, parts(std::min(A, end)) * std::min(A, end));
+    return static_cast<size_t>(most) * static_cast<size_t>(h) * 4u;
+}
+
+// Which calls stream their weights (gemm_stream), from the call's row bound and its number of
+// experts: the same answer for every launch path of a call, since the waves' K parts make its
+// sums round differently.  Measured (us, up / down (+ split sum), tiled kernels against this):
+// bf16: 1 expert 16 rows (2048 x 2048) 20 / 7 + 3 against 7 / 6, 4 experts 128 rows 22 / 11 + 4
+//   against 13 / 11, 250 rows 47 / 14 + 5 against 20 / 16; 8 experts (3072 x 1536 SwiGLU) 500
+//   rows 61 / 28 + 6 against 58 / 28 + 5; 64 experts (1024 x 4096) 1000 rows 110 / 109 against
+//   110 / 101, but 2000 rows 107 / 111 against 139 / 117; 128 experts (768 x 768) 250 rows 25 / 14
+//   + 4 against 12 / 10, 1000 rows 27 / 24 against 27 / 26;
+// fp32: 8 experts (768 x 3072) 4 rows 22 / 19 + 4 against 11 / 11, 64 rows 29 / 27 + 5 against
+//   26 / 28, 128 rows 29 / 27 + 4 against 33 / 41 (its matrix rate is a sixteenth of bf16's);
+//   only where the tiled kernel's up-projection has at most one 128-column tile per CU: with
+//   more, its 128-byte pieces of a row stream the weights faster (layers of 24 experts 3456 x 488
+//   167 -> 136, 64 experts 2624 x 168 203 -> 173, but 96 experts 832 x 1216 112 -> 136, 64 experts
+//   640 x 2564 209 -> 253).
+inline bool stream_rows(int64_t A, int E, int64_t fp, bool bf16, int cus) {
+    if (bf16) return A <= 512 || A <= 16 * static_cast<int64_t>(E);
+    return (A <= 64 || A <= 8 * static_cast<int64_t>(E)) && std::min<int64_t>(A, E) * (fp / 128) <= cus;
+}
+
+// The tiled bf16 launches: activation rows x weight rows of a tile.
+enum GemmShape {
+    kTurns256x256,  // gemm_turns
+    kPairs128x256,  // gemm_up_pairs
+    kRows128x256,   // gemm_bf16_lds on row-major weights
+    kTile64x128,    // gemm_bf16_lds, as the rest
+    kTile64x256,
+    kTile128x128,
+    kTile128x256,
+    kTile128x384,
+};
+
+// Which launches take gemm_turns.  Measured over A = 3000 .. 65536 rows, 8 .. 64 experts,
+// K = 512 .. 4096 (us, the 128 x 256 tiles against 256 x 256):
+// down-projection: K = 4096 545 / 491 (1024 rows per expert), 302 / 288 (512), 213 / 210 (256);
+//   K = 2816 67 / 64 (188); K = 1792 140 / 138; but K = 1024 28 / 27 (128), K = 512 37 / 44 (512):
+//   a short K loop does not pay for its fill and the single workgroup's exposed epilogue;
+// up-projection: K = 4096 941 / 799, 369 / 307, 262 / 219 and, in less than one round of tiles,
+//   141 / 124, but 137 / 173 where the tiles are just over one round of the CUs; K = 2048
+//   419 / 378 over many rounds, a tie below; K = 1024 702 / 708.
+inline bool turns_rows(int64_t A, int E) { return A >= 192 * static_cast<int64_t>(E); }
+inline bool turns_down(int64_t A, int E, int K) { return K >= 1536 && turns_rows(A, E); }
+inline bool turns_up(int64_t A, int E, int K, int64_t n_tiles, int cus) {
+    if (K % 32 != 0 || K < 1536 || !turns_rows(A, E)) return false;
+    // expected rounds of tiles: half an empty row tile per expert
+    const double rounds = (static_cast<double>(A) / 256 + 0.5 * E) * static_cast<double>(n_tiles) / cus;
+    return rounds >= 4 || (K >= 3072 && (rounds >= 1.6 || (rounds <= 1 && rounds >= 0.75)));
+}
+
+// Tile shape otherwise: 128 activation rows x 256 weight rows, 32-wide K steps, three stages (two in
+// flight) in 72 KiB of LDS, so that two workgroups share a CU and one's epilogue and pipeline fill
+// overlap the other's MFMAs.  The up-projection takes its activation rows in 128-byte pieces when
+// K allows it (gemm_up_pairs).  Its weights are K-blocked when K = h is a multiple of 32; otherwise
+// they are row-major (1531 tokens, 24 experts, h = 776, f = 1365: 34.5 us, 49.7 through a
+// register-staged kernel).  The down-projection's K is fp, always a multiple of 128.
+//
+// Few tiles leave CUs idle and few bytes in flight, so such calls take smaller ones.  Measured
+// (us, up / down; each output element's K sum is the same in any shape):
+// - experts that average at most 48 rows, 64 x 256: 64 experts (1024 x 1024) 2000 rows 34 / 35
+//   -> 30 / 30, 3000 rows 42 / 42 -> 38 / 37; 4000 rows would lose (35 / 32 -> 40 / 39);
+// - at most 5/8 of a 128 x 256 tile per CU, 128 x 128 in four stages, two workgroups a CU: 16
+//   experts (1408 x 1024) 2000 rows 34 / 27 -> 25 / 19; 8 experts (3072 x 384 SwiGLU) 4000 rows up
+//   65 -> 39; 24 experts (776 x 1365) 3062 rows down 33 -> 22; at 3/4 of a tile 31 -> 34, 25 -> 28;
+// - at most 1/4, 64 x 128 for the up-projection: 4 experts (1728 x 1520) 823 rows 40 -> 18 (24 at
+//   128 x 128).
+inline bool thin_experts(int64_t A, int E) { return A <= 48 * static_cast<int64_t>(E); }
+
+// Tiles of 128 rows with half an empty row tile per expert.
+inline double expected_tiles(int64_t A, int E, int64_t n_tiles) {
+    return (static_cast<double>(A) / 128 + 0.5 * E) * static_cast<double>(n_tiles);
+}
+
+inline GemmShape up_shape(int64_t A, int E, int K, int N, bool swiglu, int cus) {
+    const int64_t n_tiles = tiles_of(N, swiglu ? 128 : 256);
+    if (K % 32 != 0) return kRows128x256;
+    if (turns_up(A, E, K, n_tiles, cus)) return kTurns256x256;
+    if (thin_experts(A, E)) return kTile64x256;
+    const double tiles = expected_tiles(A, E, n_tiles);
+    if (4 * tiles <= cus) return kTile64x128;
+    if (8 * tiles <= 5 * cus) return kTile128x128;
+    return K % 64 == 0 ? kPairs128x256 : kTile128x256;
+}
+
+// When the down-projection's tiles fit on the CUs in one round even 384 columns wide, and those
+// waste no more columns than 256-wide ones, it runs 128 x 384 tiles, one workgroup per CU with
+// 96 KiB of stages: every tile then streams its weights with more bytes in flight instead of a
+// third of the CUs taking a second tile (64 experts, 3072 x 768, 8192 rows 108 -> 89; 1024 columns
+// in three would lose: 26 -> 30).  That workgroup has 8 waves (2 x 4, each 64 x 96), two per SIMD, so
+// that one wave's LDS reads, loads and barrier waits overlap the other's MFMAs.
+inline GemmShape down_shape(int64_t A, int E, int K, int N, int cus) {
+    const bool fits_384 = tiles_of(N, 384) * 384 <= tiles_of(N, 256) * 256 && row_tile_bound(A, E, 128) * tiles_of(N, 384) <= cus;
+    // 32 experts (1568 x 640), 9542 rows: the layer 101 us at 384 columns, 105 in turns; from
+    // 375 rows per expert turns win there too (48.6 -> 45.2)
+    if (turns_down(A, E, K) && !(fits_384 && A < 320 * static_cast<int64_t>(E))) return kTurns256x256;
+    if (thin_experts(A, E)) return kTile64x256;
+    if (8 * expected_tiles(A, E, tiles_of(N, 256)) <= 5 * cus) return kTile128x128;
+    return fits_384 ? kTile128x384 : kTile128x256;
 }
 
 }  // namespace moe
