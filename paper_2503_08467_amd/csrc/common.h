@@ -87,6 +87,26 @@ __device__ __forceinline__ float act_gelu_fast(float u) {
     return fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_amdgcn_fmed3f(u, 0.f, __builtin_inff()));
 }
 
+// act_gelu_fast with p of degree 10: 2.4e-7 at most and 2.1e-8 root mean square, where
+// 0.5 u (1 + erff) has 4.5e-7 and 2.5e-8 and no digit left in the tail.  An infinity gives itself
+// or, below zero, NaN, as it does there.
+__device__ __forceinline__ float act_gelu_near(float u) {
+    const float a = fabsf(u);
+    float p = -7.46755095e-09f;
+    p = fmaf(p, a, 2.90787827e-07f);
+    p = fmaf(p, a, -4.67541513e-06f);
+    p = fmaf(p, a, 3.87351075e-05f);
+    p = fmaf(p, a, -1.46217167e-04f);
+    p = fmaf(p, a, -2.85693500e-04f);
+    p = fmaf(p, a, 7.31283934e-03f);
+    p = fmaf(p, a, -5.27087918e-02f);
+    p = fmaf(p, a, -4.59119996e-01f);
+    p = fmaf(p, a, -1.15111982e+00f);
+    p = fmaf(p, a, -9.99999538e-01f);
+    const float r = fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_amdgcn_fmed3f(u, 0.f, __builtin_inff()));
+    return a < __builtin_inff() ? r : u * __builtin_amdgcn_fmed3f(u, 0.f, 1.f);
+}
+
 // 0.5 u (1 + tanh(z)) = u / (1 + e^(-2 z)), z = sqrt(2 / pi) (u + 0.044715 u^3), with the
 // hardware exponential and reciprocal: no cancellation in the negative tail (relative errors
 // there below 4e-6 down to -6, where 1 + tanhf leaves no digit; root mean square over N(0, 1)
