@@ -1878,26 +1878,27 @@ hipError_t run_stream_t(GroupedGemm g, int64_t A_max, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
-// Weight rows per workgroup: as many of 64, 32, 16 as still give every CU two workgroups (one
-// from 48 rows on, where narrow ones re-read the activations too often: 1 expert, 64 rows 10.2 / 8.0
-// us at 32, 8.4 / 7.2 at 64; 8 experts, 4 fp32 rows 12.9 at 32, 10.9 at 16).  Row tiles of 32 where
-// experts average more than 8 rows (8 experts, 256 rows 77 / 35 -> 68 / 30 us; 64 experts, 64 rows
-// 17.0 -> 18.4 us would lose).
 template <typename T, int EPI, bool OB>
 hipError_t run_stream(GroupedGemm g, int64_t A_max, hipStream_t s) {
-    constexpr int kMin = EPI == kEpiSwiglu ? 32 : 16;
-    const int64_t tiles = std::min<int64_t>(A_max, g.E + A_max / 16);
-    const int64_t want = (A_max < 48 ? 2 : 1) * static_cast<int64_t>(device_cus());
-    int nc = 64;
-    while (nc > kMin && tiles * ceil_div(g.N, EPI == kEpiSwiglu ? nc / 2 : nc) < want) nc /= 2;
-    if constexpr (kMin == 16) {
+    constexpr bool kDual = EPI == kEpiSwiglu, kBf = std::is_same<T, bf16_t>::value;
+    const int nc = stream_width(A_max, g.E, g.N, kDual, device_cus());
+    if constexpr (!kDual) {
         if (nc == 16) return run_stream_t<T, EPI, OB, 16, 1>(g, A_max, s);
     }
     if (nc == 32) return run_stream_t<T, EPI, OB, 32, 1>(g, A_max, s);
-    if constexpr (std::is_same<T, bf16_t>::value) {
-        if (A_max > 8 * static_cast<int64_t>(g.E)) return run_stream_t<T, EPI, OB, 64, 2>(g, A_max, s);
+    if constexpr (kBf) {
+        const int blocks = stream_launch_blocks(A_max, g.E, ceil_div(g.N, kDual ? 32 : 64), kBf, device_cus());
+        if (blocks == 3) return run_stream_t<T, EPI, OB, 64, 3>(g, A_max, s);
+        if (blocks == 2) return run_stream_t<T, EPI, OB, 64, 2>(g, A_max, s);
     }
     return run_stream_t<T, EPI, OB, 64, 1>(g, A_max, s);
+}
+
+// An up-projection's tiles on K-blocked weights, or on row-major ones.
+template <int BM, int BW, int NS, int EPI>
+hipError_t run_bf16_up(GroupedGemm g, int64_t A_max, hipStream_t s) {
+    if (g.K % 32 == 0) return run_bf16_lds<BM, BW, 32, NS, EPI, true>(g, A_max, s);
+    return run_bf16_lds<BM, BW, 32, NS, EPI, true, 2, true>(g, A_max, s);
 }
 
 template <int EPI, bool OB>
@@ -1906,12 +1907,11 @@ hipError_t run_bf16_best(GroupedGemm g, int64_t A_max, hipStream_t s) {
         static_assert(OB, "H is bf16");
         switch (up_shape(A_max, g.E, g.K, g.N, EPI == kEpiSwiglu, device_cus())) {
             case kTurns256x256: return run_turns<EPI, OB>(g, A_max, s);
-            case kTile64x256: return run_bf16_lds<64, 256, 32, 3, EPI, OB>(g, A_max, s);
-            case kTile64x128: return run_bf16_lds<64, 128, 32, 3, EPI, OB>(g, A_max, s);
-            case kTile128x128: return run_bf16_lds<128, 128, 32, 4, EPI, OB>(g, A_max, s);
+            case kTile64x256: return run_bf16_up<64, 256, 3, EPI>(g, A_max, s);
+            case kTile64x128: return run_bf16_up<64, 128, 3, EPI>(g, A_max, s);
+            case kTile128x128: return run_bf16_up<128, 128, 4, EPI>(g, A_max, s);
             case kPairs128x256: return run_up_pairs<EPI>(g, A_max, s);
-            case kTile128x256: return run_bf16_lds<128, 256, 32, 3, EPI, OB>(g, A_max, s);
-            case kRows128x256: return run_bf16_lds<128, 256, 32, 3, EPI, OB, 2, true>(g, A_max, s);
+            case kTile128x256: return run_bf16_up<128, 256, 3, EPI>(g, A_max, s);
             default: return hipErrorInvalidValue;
         }
     } else {
@@ -1996,7 +1996,7 @@ hipError_t ffn_pair(const void* x_perm, const int32_t* offsets, int64_t grid_row
                     int call_E = 0) {
     if (grid_rows == 0) return hipSuccess;
     // call_E: the call's experts where this launch covers one of them
-    const bool stream = stream_rows(rows_max, call_E ? call_E : E, fp, bf16, device_cus());
+    const bool stream = stream_rows(rows_max, call_E ? call_E : E, h, fp, act == MOE_ACT_SWIGLU, bf16, device_cus());
     GroupedGemm g1{};
     g1.a = x_perm;
     g1.gather = gather;

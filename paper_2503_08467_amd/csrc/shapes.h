@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 namespace moe {
 
@@ -114,30 +115,71 @@ inline size_t down_partial_bytes(int64_t A, int64_t h, int64_t fp, bool bf16) {
     return static_cast<size_t>(most) * static_cast<size_t>(h) * 4u;
 }
 
-// Which calls stream their weights (gemm_stream), from the call's row bound and its number of
-// experts: the same answer for every launch path of a call, since the waves' K parts make its
-// sums round differently.  Measured (us, up / down (+ split sum), tiled kernels against this):
-// bf16: 1 expert 16 rows (2048 x 2048) 20 / 7 + 3 against 7 / 6, 4 experts 128 rows 22 / 11 + 4
-//   against 13 / 11, 250 rows 47 / 14 + 5 against 20 / 16; 8 experts (3072 x 1536 SwiGLU) 500
-//   rows 61 / 28 + 6 against 58 / 28 + 5; 64 experts (1024 x 4096) 1000 rows 110 / 109 against
-//   110 / 101, but 2000 rows 107 / 111 against 139 / 117; 128 experts (768 x 768) 250 rows 25 / 14
-//   + 4 against 12 / 10, 1000 rows 27 / 24 against 27 / 26;
-// fp32: 8 experts (768 x 3072) 4 rows 22 / 19 + 4 against 11 / 11, 64 rows 29 / 27 + 5 against
-//   26 / 28, 128 rows 29 / 27 + 4 against 33 / 41 (its matrix rate is a sixteenth of bf16's);
-//   only where the tiled kernel's up-projection has at most one 128-column tile per CU: with
-//   more, its 128-byte pieces of a row stream the weights faster (layers of 24 experts 3456 x 488
-//   167 -> 136, 64 experts 2624 x 168 203 -> 173, but 96 experts 832 x 1216 112 -> 136, 64 experts
-//   640 x 2564 209 -> 253).
-inline bool stream_rows(int64_t A, int E, int64_t fp, bool bf16, int cus) {
-    if (bf16) return A <= 512 || A <= 16 * static_cast<int64_t>(E);
-    return (A <= 64 || A <= 8 * static_cast<int64_t>(E)) && std::min<int64_t>(A, E) * (fp / 128) <= cus;
+// Weight rows per workgroup of gemm_stream (SwiGLU: of both matrices together): as many of 64, 32, 16
+// as still give every CU two workgroups (one from 48 rows on, where narrow ones re-read the
+// activations too often: 1 expert, 64 rows 10.2 / 8.0 us at 32, 8.4 / 7.2 at 64; 8 experts, 4 fp32 rows
+// 12.9 at 32, 10.9 at 16).
+inline int stream_width(int64_t A, int E, int64_t N, bool swiglu, int cus) {
+    const int64_t tiles = std::min<int64_t>(A, E + A / 16), want = (A < 48 ? 2 : 1) * static_cast<int64_t>(cus);
+    int nc = 64;
+    while (nc > (swiglu ? 32 : 16) && tiles * tiles_of(N, swiglu ? nc / 2 : nc) < want) nc /= 2;
+    return nc;
+}
+
+// Blocks of 16 activation rows per workgroup of gemm_stream (of 64 weight rows; narrower ones take
+// one) that suit a call's rows per expert: two
+// above 8 (8 experts, 256 rows 77 / 35 -> 68 / 30 us; 64 experts, 64 rows 17.0 -> 18.4 us would lose);
+// three where the experts' rows, with the spread of an even routing, need fewer tiles of 48 than of 32
+// (512 rows: 16 experts, 1024 x 4096 82 -> 69 us, 8 experts 69 -> 57; but 24 rows each 64 -> 66, 96 rows
+// 45 -> 49).
+inline int stream_blocks(int64_t A, int E, bool bf16) {
+    if (!bf16 || A <= 8 * static_cast<int64_t>(E)) return 1;
+    const double rows = static_cast<double>(A) / E, most = rows + 1.3 * std::sqrt(rows);
+    return E >= 4 && rows <= 72 && std::ceil(most / 48) < std::ceil(most / 32) ? 3 : 2;
+}
+
+// The same for a launch of n_tiles column tiles of 64: three only where two would give the CUs more
+// than 1.2 workgroups each (8 experts, 1024 x 1024, the layer: 256 rows 22.9 us at two, 24.5 at three;
+// 512 rows 29.1 and 24.5).
+inline int stream_launch_blocks(int64_t A, int E, int64_t n_tiles, bool bf16, int cus) {
+    const int blocks = stream_blocks(A, E, bf16);
+    return blocks == 3 && (static_cast<double>(A) / 32 + 0.5 * E) * static_cast<double>(n_tiles) <= 1.2 * cus ? 2 : blocks;
+}
+
+// Which calls stream their weights (gemm_stream), from the call's sizes: the same answer for every
+// launch path of a call, since the waves' K parts make its sums round differently.
+//
+// bf16: a streaming call reads an expert's W bytes of weights once per row tile, the first time from
+// HBM, again from L2 at about 10 TB/s; the tiled kernels read them once and take the longer of that
+// and of their K loops, 9 ns per element of h + fp.  So it streams where the re-reads (of half a tile
+// more per expert than its rows fill) stay below what the K loops take longer than HBM.  The tiled
+// kernels' row-major form (h not a multiple of 32) reads its weights more slowly.  Measured (us, the
+// expert step, streamed / tiled): 1 expert (4096 x 3584 SwiGLU) 128 rows 56 / 85, 256 94 / 86, 512 153 / 90;
+//   (2048 x 2048) 512 rows 37 / 45, 768 52 / 45; 4 experts (4096 x 1792 SwiGLU) 192 rows 64 / 76, 256 80 /
+//   76; 8 experts (4096 x 3584 SwiGLU) 64 rows 136 / 129, 192 148 / 131, 512 244 / 138; (2048 x 2048) 384
+//   rows 50 / 61, 512 64 / 61; 24 experts (1032 x 4096) 512 rows 110 / 127; 64 experts (1024 x 4096) 1000
+//   rows 213 / 200.  With more than 512 rows, only up to 16 an expert.
+// fp32: 8 experts (768 x 3072, up / down + split sum, tiled against streamed) 4 rows 22 / 19 + 4
+//   against 11 / 11, 64 rows 29 / 27 + 5 against 26 / 28, 128 rows 29 / 27 + 4 against 33 / 41 (its
+//   matrix rate is a sixteenth of bf16's); only where the tiled kernel's up-projection has at most
+//   one 128-column tile per CU: with more, its 128-byte pieces of a row stream the weights faster
+//   (layers of 24 experts 3456 x 488 167 -> 136, 64 experts 2624 x 168 203 -> 173, but 96 experts 832 x
+//   1216 112 -> 136, 64 experts 640 x 2564 209 -> 253).
+inline bool stream_rows(int64_t A, int E, int64_t h, int64_t fp, bool swiglu, bool bf16, int cus) {
+    if (!bf16) return (A <= 64 || A <= 8 * static_cast<int64_t>(E)) && std::min<int64_t>(A, E) * (fp / 128) <= cus;
+    if (A > 512 && A > 16 * static_cast<int64_t>(E)) return false;
+    const double weights = 2.0 * (swiglu ? 3 : 2) * static_cast<double>(h) * static_cast<double>(fp);
+    const double experts = static_cast<double>(std::min<int64_t>(A, E));
+    const double tile = 16.0 * std::max(2, stream_blocks(A, E, true));
+    const double again = std::max(static_cast<double>(A) / tile - experts / 2, 0.0) * weights;
+    const double first = (h % 32 == 0 ? 1.2 : 0.8) * experts * weights;
+    return again <= std::max(85e3 * static_cast<double>(h + fp) - first, 0.0);
 }
 
 // The tiled bf16 launches: activation rows x weight rows of a tile.
 enum GemmShape {
     kTurns256x256,  // gemm_turns
     kPairs128x256,  // gemm_up_pairs
-    kRows128x256,   // gemm_bf16_lds on row-major weights
     kTile64x128,    // gemm_bf16_lds, as the rest
     kTile64x256,
     kTile128x128,
@@ -145,11 +187,19 @@ enum GemmShape {
     kTile128x384,
 };
 
-// Which launches take gemm_turns.  Measured over A = 3000 .. 65536 rows, 8 .. 64 experts,
+// Expected rounds of 256 x 256 tiles over the CUs: half an empty row tile per expert.
+inline double turns_rounds(int64_t A, int E, int64_t n_tiles, int cus) {
+    return (static_cast<double>(A) / 256 + 0.5 * E) * static_cast<double>(n_tiles) / cus;
+}
+
+// Which launches take gemm_turns.  Measured over A = 768 .. 65536 rows, 1 .. 64 experts,
 // K = 512 .. 4096 (us, the 128 x 256 tiles against 256 x 256):
 // down-projection: K = 4096 545 / 491 (1024 rows per expert), 302 / 288 (512), 213 / 210 (256);
 //   K = 2816 67 / 64 (188); K = 1792 140 / 138; but K = 1024 28 / 27 (128), K = 512 37 / 44 (512):
-//   a short K loop does not pay for its fill and the single workgroup's exposed epilogue;
+//   a short K loop does not pay for its fill and the single workgroup's exposed epilogue; and where
+//   the 128 x 256 tiles have a CU each they win (16 experts, 1024 x 4096, 6144 rows 158 / 168 the
+//   step, but 8192 rows 204 / 189; 8 experts, 4096 x 3584, 1536 rows 210 / 222, but 4 experts, 2048
+//   rows 237 / 210);
 // up-projection: K = 4096 941 / 799, 369 / 307, 262 / 219 and, in less than one round of tiles,
 //   141 / 124, but 137 / 173 where the tiles are just over one round of the CUs; K = 2048
 //   419 / 378 over many rounds, a tie below; K = 1024 702 / 708.
@@ -157,8 +207,7 @@ inline bool turns_rows(int64_t A, int E) { return A >= 192 * static_cast<int64_t
 inline bool turns_down(int64_t A, int E, int K) { return K >= 1536 && turns_rows(A, E); }
 inline bool turns_up(int64_t A, int E, int K, int64_t n_tiles, int cus) {
     if (K % 32 != 0 || K < 1536 || !turns_rows(A, E)) return false;
-    // expected rounds of tiles: half an empty row tile per expert
-    const double rounds = (static_cast<double>(A) / 256 + 0.5 * E) * static_cast<double>(n_tiles) / cus;
+    const double rounds = turns_rounds(A, E, n_tiles, cus);
     return rounds >= 4 || (K >= 3072 && (rounds >= 1.6 || (rounds <= 1 && rounds >= 0.75)));
 }
 
@@ -166,19 +215,31 @@ inline bool turns_up(int64_t A, int E, int K, int64_t n_tiles, int cus) {
 // flight) in 72 KiB of LDS, so that two workgroups share a CU and one's epilogue and pipeline fill
 // overlap the other's MFMAs.  The up-projection takes its activation rows in 128-byte pieces when
 // K allows it (gemm_up_pairs).  Its weights are K-blocked when K = h is a multiple of 32; otherwise
-// they are row-major (1531 tokens, 24 experts, h = 776, f = 1365: 34.5 us, 49.7 through a
-// register-staged kernel).  The down-projection's K is fp, always a multiple of 128.
+// they are row-major and the kernel's RM form reads them, in the same shapes (1531 tokens, 24 experts,
+// h = 776, f = 1365: 34.5 us, 49.7 through a register-staged kernel).  The down-projection's K is fp,
+// always a multiple of 128.
 //
 // Few tiles leave CUs idle and few bytes in flight, so such calls take smaller ones.  Measured
 // (us, up / down; each output element's K sum is the same in any shape):
-// - experts that average at most 48 rows, 64 x 256: 64 experts (1024 x 1024) 2000 rows 34 / 35
-//   -> 30 / 30, 3000 rows 42 / 42 -> 38 / 37; 4000 rows would lose (35 / 32 -> 40 / 39);
+// - thin experts, 64 x 256: 64 experts (1024 x 1024) 2000 rows 34 / 35 -> 30 / 30; and where one row tile
+//   each gives every CU at most one 128-column tile, 64 x 128 up and 128 x 128 down: 32 experts (1024 x
+//   4096) 1024 rows the layer 126 -> 111; 16 experts (2048 x 2048) 512 rows 81 -> 70; with more columns
+//   than that 64 experts (768 x 768) 1536 rows 45 -> 53;
 // - at most 5/8 of a 128 x 256 tile per CU, 128 x 128 in four stages, two workgroups a CU: 16
 //   experts (1408 x 1024) 2000 rows 34 / 27 -> 25 / 19; 8 experts (3072 x 384 SwiGLU) 4000 rows up
 //   65 -> 39; 24 experts (776 x 1365) 3062 rows down 33 -> 22; at 3/4 of a tile 31 -> 34, 25 -> 28;
 // - at most 1/4, 64 x 128 for the up-projection: 4 experts (1728 x 1520) 823 rows 40 -> 18 (24 at
 //   128 x 128).
-inline bool thin_experts(int64_t A, int E) { return A <= 48 * static_cast<int64_t>(E); }
+
+// Experts whose rows fit one tile of 64: at most 40 on average, or 48 where the CUs' last round has
+// room for a few second tiles.  An even routing's largest expert passes 64 rows from about 44 on, and
+// where the tiles fill whole rounds its second row tile costs most of another (64 experts, 1024 x
+// 1024, 3000 rows 62 -> 81 us the step; 64 experts, 1024 x 4096 208 -> 259; with room 768 x 768 43 -> 44).
+inline bool thin_experts(int64_t A, int E, int64_t n_tiles, int cus) {
+    if (A <= 40 * static_cast<int64_t>(E)) return true;
+    const int64_t last = E * n_tiles % cus;
+    return A <= 48 * static_cast<int64_t>(E) && last > 0 && last + 4 * n_tiles <= cus;
+}
 
 // Tiles of 128 rows with half an empty row tile per expert.
 inline double expected_tiles(int64_t A, int E, int64_t n_tiles) {
@@ -187,9 +248,8 @@ inline double expected_tiles(int64_t A, int E, int64_t n_tiles) {
 
 inline GemmShape up_shape(int64_t A, int E, int K, int N, bool swiglu, int cus) {
     const int64_t n_tiles = tiles_of(N, swiglu ? 128 : 256);
-    if (K % 32 != 0) return kRows128x256;
     if (turns_up(A, E, K, n_tiles, cus)) return kTurns256x256;
-    if (thin_experts(A, E)) return kTile64x256;
+    if (thin_experts(A, E, n_tiles, cus)) return E * tiles_of(N, swiglu ? 64 : 128) <= cus ? kTile64x128 : kTile64x256;
     const double tiles = expected_tiles(A, E, n_tiles);
     if (4 * tiles <= cus) return kTile64x128;
     if (8 * tiles <= 5 * cus) return kTile128x128;
@@ -201,14 +261,18 @@ inline GemmShape up_shape(int64_t A, int E, int K, int N, bool swiglu, int cus) 
 // 96 KiB of stages: every tile then streams its weights with more bytes in flight instead of a
 // third of the CUs taking a second tile (64 experts, 3072 x 768, 8192 rows 108 -> 89; 1024 columns
 // in three would lose: 26 -> 30).  That workgroup has 8 waves (2 x 4, each 64 x 96), two per SIMD, so
-// that one wave's LDS reads, loads and barrier waits overlap the other's MFMAs.
+// that one wave's LDS reads, loads and barrier waits overlap the other's MFMAs.  With a short K the
+// wasted columns cost less than the second tiles do (16 experts, 1024 x 1024, 8192 rows the step 79 ->
+// 72; 8 experts, 2048 x 1408, 4096 rows 113 -> 103; but K = 2048 16 experts, 3072 rows 99 -> 106).
 inline GemmShape down_shape(int64_t A, int E, int K, int N, int cus) {
-    const bool fits_384 = tiles_of(N, 384) * 384 <= tiles_of(N, 256) * 256 && row_tile_bound(A, E, 128) * tiles_of(N, 384) <= cus;
+    const int64_t n256 = tiles_of(N, 256), n384 = tiles_of(N, 384), row_tiles = row_tile_bound(A, E, 128);
+    if (thin_experts(A, E, n256, cus)) return E * tiles_of(N, 128) <= cus ? kTile128x128 : kTile64x256;
+    if (8 * expected_tiles(A, E, n256) <= 5 * cus) return kTile128x128;
+    const bool fits_384 = row_tiles * n384 <= cus && (n384 * 384 <= n256 * 256 || (K < 1536 && row_tiles * n256 > cus));
     // 32 experts (1568 x 640), 9542 rows: the layer 101 us at 384 columns, 105 in turns; from
     // 375 rows per expert turns win there too (48.6 -> 45.2)
-    if (turns_down(A, E, K) && !(fits_384 && A < 320 * static_cast<int64_t>(E))) return kTurns256x256;
-    if (thin_experts(A, E)) return kTile64x256;
-    if (8 * expected_tiles(A, E, tiles_of(N, 256)) <= 5 * cus) return kTile128x128;
+    if (turns_down(A, E, K) && expected_tiles(A, E, n256) > cus && !(fits_384 && A < 320 * static_cast<int64_t>(E)))
+        return kTurns256x256;
     return fits_384 ? kTile128x384 : kTile128x256;
 }
 

@@ -16,6 +16,23 @@ _MAIN = r"""
 #include <iostream>
 #include <string>
 using namespace moe;
+static const char* name(GemmShape s) {
+    switch (s) {
+        case kTurns256x256: return "turns";
+        case kPairs128x256: return "pairs";
+        case kTile64x128: return "64x128";
+        case kTile64x256: return "64x256";
+        case kTile128x128: return "128x128";
+        case kTile128x256: return "128x256";
+        case kTile128x384: return "128x384";
+    }
+    return "?";
+}
+static std::string streamed(int64_t A, int E, int64_t N, bool swiglu, bool bf16, int cus) {
+    const int nc = stream_width(A, E, N, swiglu, cus);
+    const int blocks = nc == 64 ? stream_launch_blocks(A, E, tiles_of(N, swiglu ? 32 : 64), bf16, cus) : 1;
+    return std::to_string(nc) + "x" + std::to_string(blocks);
+}
 int main() {
     std::string what;
     while (std::cin >> what) {
@@ -26,6 +43,17 @@ int main() {
             if (route_in_lds(bf16, h, E)) { std::cout << "lds" << (group ? " grouped" : "") << "\n"; continue; }
             const int b = route_blocks(T, E, group, cus);
             std::cout << b << " x " << route_stage(E, b, route_run(bf16, h, E)) << (group ? " grouped" : "") << "\n";
+        } else if (what == "ffn") {  // bf16 A E h f swiglu cus: up / down
+            int bf16, E, h, swiglu, cus; int64_t A, f;
+            std::cin >> bf16 >> A >> E >> h >> f >> swiglu >> cus;
+            const int64_t fp = (f + 127) / 128 * 128;
+            if (stream_rows(A, E, h, fp, swiglu, bf16, cus))
+                std::cout << "stream " << streamed(A, E, fp, swiglu, bf16, cus) << " / " << streamed(A, E, h, false, bf16, cus);
+            else if (!bf16) std::cout << "fp32";
+            else std::cout << name(up_shape(A, E, h, static_cast<int>(fp), swiglu, cus)) << " / "
+                           << name(down_shape(A, E, static_cast<int>(fp), h, cus));
+            std::cout << (hands_over_sums(A, fp, bf16) ? " sums " + std::to_string(down_parts(A, fp, bf16,
+                          stream_rows(A, E, h, fp, swiglu, bf16, cus))) : "") << "\n";
         }
     }
 }
@@ -75,4 +103,51 @@ ROUTE_FORMS = [
     ("bf16", 4099, 264, 200, 2, "2 x 1"),           # E > 128: two blocks past one round of the CUs
     ("f32", 4097, 72, 256, 3, "2 x 1"),
     ("bf16", 4096, 264, 200, 2, "1 x 1"),
+]
+
+# (rows per expert, h, f, act) -> tiles of the bf16 expert step, up / down
+TILE_FORMS = [
+    ([37] * 14 + [40, 64, 0], 96, 200, "gelu", "64x128 / 128x128"),      # thin experts, few columns
+    ([20] * 127 + [64], 384, 384, "gelu", "64x256 / 64x256"),            # ... many
+    ([20] * 127 + [64], 384, 200, "swiglu", "64x256 / 64x256"),
+    ([47] * 100 + [65, 1], 192, 384, "gelu", "64x256 / 128x128"),        # 48 rows each, room in the last round
+    ([600, 129, 1], 160, 300, "gelu", "64x128 / 128x128"),               # at most a quarter of a tile per CU
+    ([600, 129, 1], 160, 300, "swiglu", "64x128 / 128x128"),
+    ([900, 900, 127, 700], 544, 1300, "gelu", "128x128 / 128x128"),      # ... 5/8
+    ([900, 900, 127, 700], 544, 640, "swiglu", "128x128 / 128x128"),
+    ([900, 900, 127, 700], 544, 1300, "swiglu", "128x256 / 128x128"),    # h not a multiple of 64
+    ([128] * 119 + [129], 288, 136, "gelu", "128x256 / 128x384"),
+    ([3000, 2500, 1, 2499], 768, 640, "gelu", "pairs / 128x384"),
+    ([1024] * 7 + [1000, 24], 1024, 256, "gelu", "128x128 / 128x384"),   # short K: wasted columns
+    ([128] * 119 + [129], 256, 136, "gelu", "pairs / 128x256"),
+    ([128] * 119 + [129], 256, 136, "swiglu", "pairs / 128x256"),
+    # h not a multiple of 32: row-major weights
+    ([600, 129, 1], 168, 300, "gelu", "64x128 / 128x128"),
+    ([600, 129, 1], 168, 300, "swiglu", "64x128 / 128x128"),
+    ([20] * 127 + [64], 200, 384, "gelu", "64x256 / 128x128"),
+    ([20] * 127 + [64], 200, 200, "swiglu", "64x256 / 128x128"),
+    ([900, 900, 127, 700], 520, 1300, "gelu", "128x128 / 128x128"),
+    ([900, 900, 127, 700], 520, 640, "swiglu", "128x128 / 128x128"),
+    ([128] * 119 + [129], 264, 136, "gelu", "128x256 / 128x384"),
+    ([128] * 119 + [129], 264, 136, "swiglu", "128x256 / 128x384"),
+]
+
+# the same for streamed weights: weight rows x blocks of 16 rows of a workgroup; "sums": the second
+# product's fp32 sums go to the combine, in so many parts
+STREAM_FORMS = [
+    ([1], 8, 1, "gelu", "stream 16x1 / 16x1"),                      # one 16-byte chunk of K: most waves have none
+    ([16, 0, 17, 1, 15], 200, 129, "gelu", "stream 16x1 / 16x1"),   # row-tile edges; K ends inside a step
+    ([5] * 40, 136, 640, "gelu", "stream 64x1 / 32x1 sums 1"),
+    ([64, 0], 1544, 300, "gelu", "stream 16x1 / 32x1"),
+    ([300, 212], 64, 1000, "gelu", "stream 64x2 / 16x1 sums 1"),    # 512 rows: the most at any number of experts
+    ([9] * 72, 32, 96, "gelu", "stream 32x1 / 16x1"),               # 648 rows: streamed for their number of experts
+    # 32 rows each on average: three blocks, around their edges (47, 48, 49, more than two tiles)
+    ([32, 48, 49, 16, 47, 0, 33, 31, 97, 10, 32, 30, 20, 40, 3, 24], 1104, 1100, "gelu", "stream 64x3 / 64x3 sums 1"),
+    ([32, 48, 49, 16, 47, 0, 33, 31, 97, 10, 32, 30, 20, 40, 3, 24], 200, 700, "swiglu", "stream 64x3 / 32x1 sums 1"),
+    ([9] * 72, 520, 1024, "gelu", "stream 64x2 / 64x2"),
+]
+
+# decode-sized calls on weights too large to stream: (experts, rows, h, f, act)
+SUMS_FORMS = [
+    (28, 504, 928, 900, "swiglu", "64x256 / 128x128 sums 1"),
 ]

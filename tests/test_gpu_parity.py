@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 import synth
-from _shapes import ROUTE_FORMS
+from _shapes import ROUTE_FORMS, STREAM_FORMS, SUMS_FORMS, TILE_FORMS
 from _util import by_expert, compare_routing, normwise, rowwise, to_dev
 
 torch = pytest.importorskip("torch")
@@ -351,13 +351,33 @@ def test_ffn_parity_on_random_shapes(i, counts, h, f, act, dtype):
     ([16, 0, 17, 1, 15], 200, 129),      # row-tile edges; K ends inside a step for both types
     ([0, 31, 33], 1032, 40),             # N past a 64-row block by 8; ragged K in bf16 only from 40
     ([5] * 40, 136, 64),                 # many experts, narrow shards
-    ([64, 0], 1544, 300),                # 32-row tiles for bf16 (more than 8 rows per expert)
-    ([300, 212], 64, 1000),              # 512 rows: the most that always stream in bf16
+    ([64, 0], 1544, 300),                # one expert
+    ([300, 212], 64, 1000),              # 512 rows: the most in bf16 that any number of experts stream
     ([9] * 72, 32, 96),                  # 648 rows: streamed for their number of experts (bf16)
 ])
 def test_streamed_weights(dtype, act, counts, h, f):
-    """Calls with few rows per expert: the expert step through every entry point (x_perm, fp32
-    partials, gathered rows with the combine folded in, top-1) against the oracle."""
+    _check_entry_points(dtype, act, counts, h, f)
+
+
+@pytest.mark.parametrize("counts,h,f,act,form", STREAM_FORMS)
+def test_stream_forms(counts, h, f, act, form):
+    _check_entry_points("bf16", act, counts, h, f)
+
+
+@pytest.mark.parametrize("E,A,h,f,act,form", SUMS_FORMS)
+def test_tiled_calls_hand_over_sums(E, A, h, f, act, form):
+    """Decode-sized calls on weights too large to stream: the tiled kernels write the fp32 sums
+    that the combine reads; y_perm stays unwritten."""
+    counts = np.full(E, A // E)
+    counts[: A % E] += 1
+    counts[0], counts[1] = 2 * counts[0], counts[1] - counts[0]
+    _check_entry_points("bf16", act, counts.tolist(), h, f, written=False)
+
+
+def _check_entry_points(dtype, act, counts, h, f, written=None):
+    """The expert step through every entry point (x_perm, fp32 partials, a launch per expert,
+    gathered rows with the combine folded in, top-1) against the oracle, and bit for bit against
+    each other where they round alike."""
     rng = np.random.default_rng(sum(counts) + h + 7 * f)
     x, w1, w3, w2, offsets = _ffn_case(rng, counts, h, f, act, dtype)
     dt, A = tdt(dtype), len(x)
@@ -374,10 +394,12 @@ def test_streamed_weights(dtype, act, counts, h, f):
     wt = rng.uniform(0.1, 1.0, A).astype(np.float32)
     xt, src, wd = to_dev(x[inv], dt), to_dev(perm, torch.int32), to_dev(wt, torch.float32)
     top1 = moe.expert_ffn_shard_top1(xt, src, wd, od, packed)
-    one, _ = moe.expert_ffn_shard_gather_combine(xt, src, od, to_dev(inv[:, None], torch.int32), wd[:, None].contiguous(),
-                                                 packed)
+    pos = to_dev(inv[:, None], torch.int32)
+    one, y_perm = moe.expert_ffn_shard_gather_combine(xt, src, od, pos, wd[:, None].contiguous(), packed)
     torch.cuda.synchronize()
     assert torch.equal(y, each) and torch.equal(y, y32.to(dt))
+    assert torch.equal(one, moe.combine(y, pos, wd[:, None].contiguous()))
+    assert written is None or (y_perm is not None) == written
     assert rowwise(np_of(y32), ref) <= tol and rowwise(np_of(y), ref) <= tol
     for got in (top1, one):
         assert rowwise(np_of(got), wt[:, None] * ref[inv]) <= tol
@@ -407,17 +429,11 @@ def test_hidden_size_off_the_k_block(counts, h, act):
     assert rowwise(np_of(clean), ref) <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("act", ["gelu", "swiglu"])
-@pytest.mark.parametrize("counts,h,f", [
-    ([37] * 14 + [64, 65, 0], 96, 200),   # at most 48 rows per expert: 64 x 256 tiles
-    ([600, 129, 1], 160, 300),            # at most a quarter of a tile per CU: 64 x 128 up
-    ([900, 900, 127, 700], 520, 1300),    # ... 5/8: 128 x 128, four stages
-    ([3000, 2500, 1], 768, 640),          # down 128 x 384
-    ([128] * 120, 264, 136),              # many tiles: 128 x 256
-])
-def test_tile_shapes_agree(counts, h, f, act):
-    """The tile is chosen from the call's rows, experts and columns; a launch per expert chooses
-    by that expert alone.  Bits agree, and a sample of rows matches the oracle."""
+@pytest.mark.parametrize("counts,h,f,act,form", TILE_FORMS)
+def test_tile_shapes_agree(counts, h, f, act, form):
+    """The tile is chosen from the call's rows, experts and columns (form: up- and down-projection);
+    a launch per expert chooses by that expert alone.  Bits agree, and a sample of rows matches the
+    oracle."""
     rng = np.random.default_rng(sum(counts) + h)
     x, w1, w3, w2, offsets = _ffn_case(rng, counts, h, f, act, "bf16")
     dt = torch.bfloat16

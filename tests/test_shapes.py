@@ -2,7 +2,7 @@
 no sizes ask for a form that is not compiled."""
 import itertools
 
-from _shapes import CUS, ROUTE_FORMS, ask
+from _shapes import CUS, ROUTE_FORMS, STREAM_FORMS, SUMS_FORMS, TILE_FORMS, ask
 
 
 def _route(dtype, T, h, E, k, want=1):
@@ -36,3 +36,32 @@ def test_the_kernel_of_a_token_does_not_depend_on_its_batch():
     for d, h, E in itertools.product(("bf16", "f32"), (64, 72, 4096), (1, 24, 32, 33, 64, 256)):
         got = ask([_route(d, T, h, E, 1) for T in (1, 16, 17, 64, 65, 8192, 100000)])
         assert len({g.startswith("lds") for g in got}) == 1
+
+
+def _ffn(A, E, h, f, act, dtype="bf16"):
+    return f"ffn {int(dtype == 'bf16')} {A} {E} {h} {f} {int(act == 'swiglu')} {CUS}"
+
+
+def test_expert_step_cases_reach_their_forms():
+    cases = [(sum(c), len(c), h, f, act, form) for c, h, f, act, form in TILE_FORMS + STREAM_FORMS]
+    cases += [(A, E, h, f, act, form) for E, A, h, f, act, form in SUMS_FORMS]
+    got = ask([_ffn(*c[:5]) for c in cases])
+    assert got == [c[5] for c in cases]
+
+
+def test_weights_stream_only_where_re_reading_them_pays():
+    # (rows, experts, h, f, act): measured faster streamed, and faster in tiles
+    streamed = [(128, 1, 4096, 3584, "swiglu"), (512, 1, 2048, 2048, "gelu"), (384, 8, 2048, 2048, "gelu"),
+                (512, 16, 1024, 4096, "gelu"), (512, 8, 1024, 4096, "gelu"), (512, 24, 1032, 4096, "gelu"),
+                (1024, 64, 1024, 1024, "gelu"), (192, 4, 4096, 1792, "swiglu")]
+    tiled = [(512, 1, 4096, 3584, "swiglu"), (512, 8, 4096, 3584, "swiglu"), (384, 2, 4096, 3584, "swiglu"),
+             (256, 8, 4096, 3584, "swiglu"), (512, 8, 4096, 1792, "swiglu")]
+    assert all(a.startswith("stream") for a in ask([_ffn(*c) for c in streamed]))
+    assert not any(a.startswith("stream") for a in ask([_ffn(*c) for c in tiled]))
+
+
+def test_few_tiles_take_small_ones():
+    # a long K and rows enough per expert for 256 x 256 tiles, but too few of them for the CUs
+    got = ask([_ffn(768, 1, 1024, 4096, "gelu"), _ffn(1536, 8, 1024, 4096, "gelu"), _ffn(6144, 16, 1024, 4096, "gelu"),
+               _ffn(8192, 16, 1024, 4096, "gelu"), _ffn(3008, 64, 1024, 1024, "gelu"), _ffn(3008, 64, 768, 768, "gelu")])
+    assert [a.split(" / ")[1] for a in got] == ["128x128", "128x128", "128x256", "turns", "128x256", "64x256"]
