@@ -4,6 +4,7 @@ call is made)."""
 import ctypes
 import os
 import re
+import sys
 
 import pytest
 
@@ -129,6 +130,27 @@ def test_ffn_workspace_holds_split_partials(lib):
         for h, f in [(1024, 4096), (4096, 1792), (768, 3072), (64, 128), (72, 1000)]:
             sizes = [ws(a, h, f, dt) for a in range(0, 1300, 7)]
             assert sizes == sorted(sizes), (h, f, dt)
+
+
+def test_stream_handle_without_the_private_name(monkeypatch):
+    """Where torch lacks the raw-handle function the calls take the public current stream of the
+    tensor's device; an explicit stream goes first either way."""
+    import importlib.util
+    import types
+
+    import torch
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    asked = []
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda device: asked.append(device) or types.SimpleNamespace(cuda_stream=7))
+    spec = importlib.util.spec_from_file_location("paper_2503_08467_amd._layer_without_it", moe.layer.__file__)
+    layer = importlib.util.module_from_spec(spec)
+    monkeypatch.setitem(sys.modules, spec.name, layer)  # dataclasses look the module up
+    spec.loader.exec_module(layer)
+    t = torch.empty(1)
+    assert layer._stream(t, None) == 7 and asked == [t.device]
+    assert layer._stream(t, types.SimpleNamespace(cuda_stream=9)) == 9 and len(asked) == 1
 
 
 def test_ffn_and_combine_reject_bad_arguments(lib):
