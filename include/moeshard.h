@@ -148,10 +148,10 @@ moe_status moe_pack_weights(const void *w1, const void *w3, const void *w2, int3
                             moe_dtype wdt, void *packed, size_t packed_bytes,
                             hipStream_t stream);
 
-/* Bytes of workspace moe_expert_ffn_shard needs: the activated inner rows (A_max x fp) and,
- * room for fp32 sums of the second product that a small call hands to the combine (at most
- * 2048 x h floats for bf16, 4096 x h for fp32).  Non-decreasing in A_max, so a workspace sized for a bound serves every
- * call with a smaller A_max. */
+/* Bytes of workspace moe_expert_ffn_shard needs: the activated inner rows (A_max x fp)
+ * and room for fp32 sums of a small call's second product (at most 2048 x h floats for bf16,
+ * 4096 x h for fp32).  Non-decreasing in A_max, so a workspace sized for a bound serves
+ * every call with a smaller A_max. */
 size_t moe_ffn_workspace_size(int64_t A_max, int32_t E, int64_t h, int64_t f, moe_act act,
                               moe_dtype dt);
 
@@ -160,10 +160,11 @@ size_t moe_ffn_workspace_size(int64_t A_max, int32_t E, int64_t h, int64_t f, mo
  *     y_perm[p] = act(x_perm[p] . W1_e^g) . W2_e^g        (shard g = the packed slice)
  * computed with bf16 MFMA and fp32 accumulation (dt = MOE_BF16) or fp32 arithmetic
  * (dt = MOE_F32).  The activated row is rounded to dt before the second product.  One
- * launch per matmul regardless of E; the per-expert counts are read on the device.  A call
+ * launch per matmul regardless of E (fp32 calls of at most 1024 rows may add one that sums
+ * the second product's K parts); the per-expert counts are read on the device.  A call
  * with few rows per expert sums each product's K in parts, each part in fp32, the parts
- * added in a fixed order; which calls do depends only on A_max, E, f and dt, so results are
- * deterministic and every entry point agrees bit for bit on one call.
+ * added in a fixed order; which calls do depends only on A_max, E, h, f, act, dt and the
+ * device, so results are deterministic and every entry point agrees bit for bit on one call.
  *   x_perm  [A, h] dtype dt, grouped rows from moe_dispatch
  *   offsets [E+1] int32, device; offsets[E] must not exceed A_max
  *   A_max   host-known upper bound of offsets[E] (normally T*k); sizes the launch

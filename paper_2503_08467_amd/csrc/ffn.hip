@@ -17,7 +17,7 @@
 // across K steps and tiles.  The epilogue applies the activation in fp32, rounds once, and
 // stores 16-byte runs straight from the accumulators (into K-blocked H for GEMM1).
 // Few rows per expert, both types (gemm_stream): K cut between a workgroup's waves, weights
-// streamed into registers.
+// streamed into registers.  Which kernel a call takes: shapes.h.
 // fp32, many rows (gemm_f32_lds): 32 x 128 tiles on v_mfma_f32_32x32x2_f32, row-major operands
 // in 128-byte row pieces through two direct-to-LDS stages, three workgroups per CU; calls of
 // at most 1024 rows split GEMM2's K into parts summed by split_reduce (or, with the combine
@@ -71,7 +71,8 @@ struct GroupedGemm {
     int64_t c_rows;
     // Down-projection only: sums in fp32 to partial[s][row][N] (no scale, no scatter) for a
     // kernel that adds the parts in order.  gemm_f32_lds: with ksplit > 1 every tile as ksplit
-    // parts of K / ksplit each.  gemm_stream: whole sums, one part.
+    // parts of K / ksplit each.  gemm_stream: whole sums, one part.  The bf16 tiles store theirs
+    // as fp32 output (c), so they read neither.
     int ksplit;
     float* partial;
 };
@@ -1720,8 +1721,9 @@ __global__ __launch_bounds__(256) void split_reduce(const float* __restrict__ pa
 // Steps 4 and 5 together for decode-sized calls (hands_over_sums): for token t and 8 columns,
 //     y[t] = sum over picks j of w[t, j] * round_ydt(sum over s of partial[s][pos_of[t, j]])
 // -- the second product's S parts in order (one where its sums are whole), rounded to y_perm's
-// type as the product or split_reduce stores it, then combine's weighted sum (fp32, pick order, invalid picks skipped) rounded
-// once: the same bits as the two launches, without writing or reading y_perm.
+// type as the product or split_reduce stores it, then combine's weighted sum (fp32, pick order,
+// invalid picks skipped) rounded once: the same bits as the two launches, without writing or
+// reading y_perm.
 template <bool YB, bool OB, int S>
 __global__ __launch_bounds__(256) void split_combine(const float* __restrict__ partial, int64_t rows_max,
                                                      int h, const int32_t* __restrict__ pos_of,
@@ -1933,8 +1935,6 @@ hipError_t gemm1(bool bf16, bool stream, GroupedGemm g, int64_t A_max, hipStream
     return bf16 ? run_bf16_best<EPI, true>(g, A_max, s) : run_f32<EPI, false>(g, A_max, s);
 }
 
-// Both matmuls of the expert step.  grid_rows sizes the launches (an upper bound of the
-// rows the offsets describe); rows_max is the row count of x_perm, H and y_perm.
 // Step 5 folded into the expert step (CombineArgs given, a call that hands_over_sums): the second
 // product's fp32 sums go straight into y through split_combine instead of into y_perm.
 struct CombineArgs {
@@ -1945,7 +1945,6 @@ struct CombineArgs {
     void* y;
     bool y_bf16;
 };
-
 
 template <bool OB, int S>
 hipError_t launch_split_reduce_t(const float* partial, int64_t rows_max, int h, int64_t grid_rows,
@@ -1989,6 +1988,8 @@ hipError_t launch_split_combine(bool yb, int S, const float* partial, int64_t ro
     return hipErrorInvalidValue;
 }
 
+// Both matmuls of the expert step.  grid_rows sizes the launches (an upper bound of the
+// rows the offsets describe); rows_max is the row count of x_perm, H and y_perm.
 hipError_t ffn_pair(const void* x_perm, const int32_t* offsets, int64_t grid_rows, int64_t rows_max, int E,
                     int h, int64_t fp, int act, bool bf16, const void* w1t, const void* w3t, const void* w2t,
                     void* y_perm, bool y_bf16, void* hbuf, hipStream_t s, const int32_t* gather = nullptr,
@@ -2107,12 +2108,12 @@ hipError_t launch_ffn_top1(const void* x, int64_t T, const int32_t* row_src, con
 
 // ------------------------------------------------------------------ no-allocation variant
 //
-// The workspace of one call (H, then the split second product's partial tiles) lives in a
+// The workspace of one call (H, then a small call's fp32 sums) lives in a
 // static device array instead of caller memory.  Each GPU the library runs on holds its own
 // copy of the array for the life of the process.  In host code the array's name only stands
 // in for it: the device address comes from hipGetSymbolAddress, taken once per device with
 // that device current, and only that address is ever handed to a kernel.  Nothing in the
-// array needs to start at zero (every H row and partial tile a kernel reads is written
+// array needs to start at zero (every H row and fp32 sum a kernel reads is written
 // earlier in the same call; rows of a tile past its segment only feed outputs that are not
 // stored).  Calls that overlap on one GPU share the array and race.
 namespace {

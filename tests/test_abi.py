@@ -107,24 +107,25 @@ def test_sizes_follow_the_padded_layout(lib):
 
 
 def test_ffn_workspace_holds_split_partials(lib):
-    """Small calls split the second product's K: fp32 partials of S x A_max x h follow H
-    (bf16: up to 8 parts up to 512 rows; fp32: 4 parts up to 1024 rows)."""
+    """Room for fp32 sums follows H: 4 parts x A_max x h for fp32 calls of at most 1024 rows, and up
+    to 8 parts for bf16 calls of at most 512, which use one (the sizes are kept for callers that
+    allocated by them)."""
     al = lambda v: (v + 255) // 256 * 256
     ws = lambda A, h, f, dt=_lib.MOE_BF16: lib.moe_ffn_workspace_size(A, 64, h, f, _lib.MOE_ACT_GELU, dt)
-    # decode-sized: 128 rows, fp = 4096 (128 K steps of 32) -> 8 parts
+    # decode-sized: 128 rows, fp = 4096 (128 K steps of 32): room for 8
     assert ws(128, 1024, 4096) == al(128 * 4096 * 2) + al(8 * 128 * 1024 * 4) + 256
     assert ws(256, 1024, 4096) == al(256 * 4096 * 2) + al(8 * 256 * 1024 * 4) + 256
     assert ws(512, 768, 3072) == al(512 * 3072 * 2) + al(4 * 512 * 768 * 4) + 256
-    # fp = 1792: 56 K steps, 8 parts would leave 7 per part -> 4 parts
+    # fp = 1792 (56 K steps): room for 4
     assert ws(128, 4096, 1792) == al(128 * 1792 * 2) + al(4 * 128 * 4096 * 4) + 256
-    # short K: fp = 128 has 4 steps, too few to split
+    # short K: fp = 128 hands over no sums
     assert ws(128, 1024, 128) == al(128 * 128 * 2) + 256
-    # larger calls do not split but keep the room (a workspace sized for a bound serves
+    # larger calls hand over none but keep the room (a workspace sized for a bound serves
     # every smaller call)
     assert ws(513, 768, 3072) == al(513 * 3072 * 2) + al(2048 * 768 * 4) + 256
     assert ws(128, 1024, 4096, _lib.MOE_F32) == al(128 * 4096 * 4) + al(4 * 128 * 1024 * 4) + 256
     assert ws(1025, 768, 3072, _lib.MOE_F32) == al(1025 * 3072 * 4) + al(4 * 1024 * 768 * 4) + 256
-    # fp32 with fp = 512: 16 K steps, 4 parts would leave 4 each -> no split
+    # fp32 with fp = 512 (16 K steps): one part, no room
     assert ws(128, 1024, 512, _lib.MOE_F32) == al(128 * 512 * 4) + 256
     for dt in (_lib.MOE_BF16, _lib.MOE_F32):
         for h, f in [(1024, 4096), (4096, 1792), (768, 3072), (64, 128), (72, 1000)]:

@@ -83,8 +83,8 @@ def test_route_shapes_and_bias(dtype, T, h, E, k, bias_kind):
 
 @pytest.mark.parametrize("T,h,E,k", [(1, 128, 40, 1), (17, 256, 64, 2), (64, 1024, 64, 2), (64, 128, 128, 8),
                                      (33, 64, 256, 5), (50, 192, 100, 3),
-                                     (40, 128, 32, 2),                       # 32 experts: the other kernel
-                                     (65, 128, 64, 2), (64, 128, 64, 9), (40, 1024, 32, 2)])  # separate launches
+                                     (40, 128, 32, 2),                       # 32 experts: the gate in registers
+                                     (65, 128, 64, 2), (64, 128, 64, 9), (40, 1024, 32, 2)])  # two launches: T, k, h
 @pytest.mark.parametrize("bias_kind", ["none", "row", "shared"])
 def test_route_dispatch_matches_two_calls(T, h, E, k, bias_kind):
     """moe_route_dispatch = moe_route + moe_dispatch (indices only), every output bit for bit:
@@ -307,9 +307,9 @@ def _run_ffn(x, w1, w3, w2, offsets, act, dtype, out_dtype=None, col0=0, f=None)
     ([513, 40, 0, 255], 768, 512),
     ([700, 333], 256, 200),                    # >= 512 rows per expert: 256-row tiles, ragged
     ([1100, 0, 1500, 3], 512, 384),
-    ([60, 0, 50, 9], 128, 1000),               # <= 128 rows: 128-column up tiles, K of the down in 4 parts
-    ([100, 7, 0, 120], 192, 2048),             # <= 256 rows: down K in 8 parts
-    ([200, 0, 61, 3], 256, 2048),              # <= 512 rows: down K in 4 parts
+    ([60, 0, 50, 9], 128, 1000),               # fp32: the down-projection's K in 4 parts; bf16 streams
+    ([100, 7, 0, 120], 192, 2048),             # the same with h = 192
+    ([200, 0, 61, 3], 256, 2048),              # the same with segments of several row tiles
 ])
 def test_ffn_parity(dtype, act, counts, h, f):
     rng = np.random.default_rng(sum(counts) + h + f)
@@ -335,7 +335,7 @@ def _random_ffn_shapes(n, seed=2024):
 @pytest.mark.parametrize("i,counts,h,f,act,dtype", _random_ffn_shapes(12))
 def test_ffn_parity_on_random_shapes(i, counts, h, f, act, dtype):
     """Seeded random shapes: expert count, ragged segments (some empty), hidden sizes off the
-    tile multiples, any inner width (split and unsplit second products)."""
+    tile multiples, any inner width (fp32: the second product's K whole and in parts)."""
     rng = np.random.default_rng(100 + i)
     x, w1, w3, w2, offsets = _ffn_case(rng, counts, h, f, act, dtype)
     got = _run_ffn(x, w1, w3, w2, offsets, act, dtype)
@@ -499,8 +499,8 @@ def test_wide_tiles_match_128_row_tiles(act, counts, h, f):
 @pytest.mark.parametrize("A,f", [(3000, 128), (300, 1024)])
 def test_ffn_parity_at_the_expert_limit(dtype, act, A, f):
     """256 experts (the most the library takes), most of them with a handful of rows or none:
-    the row-tile table at its full size, in the grouped launch and, below 512 rows, with the
-    second product's K split."""
+    the row-tile table at its full size, in the grouped launch and, for 300 fp32 rows, with
+    the second product's K in parts (bf16 streams both sizes)."""
     rng = np.random.default_rng(A + f)
     counts = rng.multinomial(A, rng.dirichlet(np.full(256, 0.2))).tolist()
     assert len(counts) == 256 and 0 in counts
@@ -516,7 +516,7 @@ def test_ffn_parity_at_the_expert_limit(dtype, act, A, f):
     ([300, 0, 5, 129, 128, 1], 256, 200),
     ([0, 0, 77], 72, 128),
     ([700, 333, 0], 256, 200),
-    ([60, 0, 50, 9], 128, 1000),  # split down-projection K: both paths split alike
+    ([60, 0, 50, 9], 128, 1000),  # fp32: the down-projection's K in parts, alike on both paths
 ])
 def test_per_expert_launches_match_grouped(dtype, act, counts, h, f):
     """The per-expert-launch ablation computes the same tiles as the grouped launch: equal
@@ -572,16 +572,16 @@ def test_gathered_rows_match_x_perm(dtype, act, T, k, E, h, f):
 
 
 @pytest.mark.parametrize("dtype,out_dtype", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("f32", "bf16")])
-@pytest.mark.parametrize("T,k,E,h,f,split", [
-    (64, 2, 8, 256, 1024, {"bf16": True, "f32": True}),     # decode-sized: split second product
-    (64, 2, 8, 256, 512, {"bf16": True, "f32": False}),     # fp32 K too short to split (16 steps)
-    (300, 2, 6, 128, 1024, {"bf16": False, "f32": True}),   # 600 rows: split only in fp32 (<= 1024)
-    (700, 3, 5, 64, 256, {"bf16": False, "f32": False}),    # 2100 rows: never split
+@pytest.mark.parametrize("T,k,E,h,f,sums", [  # sums: the second product hands its fp32 sums to the combine
+    (64, 2, 8, 256, 1024, {"bf16": True, "f32": True}),     # decode-sized: fp32 in 4 parts of K
+    (64, 2, 8, 256, 512, {"bf16": True, "f32": False}),     # fp32: inner width below 1024
+    (300, 2, 6, 128, 1024, {"bf16": False, "f32": True}),   # 600 rows: only in fp32 (<= 1024)
+    (700, 3, 5, 64, 256, {"bf16": False, "f32": False}),    # 2100 rows: never
     (1, 4, 9, 64, 1024, {"bf16": True, "f32": True}),       # one token
 ])
-def test_gather_combine_matches_two_calls(dtype, out_dtype, T, k, E, h, f, split):
+def test_gather_combine_matches_two_calls(dtype, out_dtype, T, k, E, h, f, sums):
     """moe_expert_ffn_shard_gather_combine = moe_expert_ffn_shard_gather + moe_combine, bit
-    for bit (one launch for the split sum and the combine when K is split, y_perm then left
+    for bit (where the second product hands over its fp32 sums one launch adds and combines them, y_perm then left
     unwritten), and within tolerance of the oracle; dropped picks are skipped."""
     rng = np.random.default_rng(T * 10 + k + h)
     x = rng.standard_normal((T, h)).astype(np.float32)
@@ -604,8 +604,8 @@ def test_gather_combine_matches_two_calls(dtype, out_dtype, T, k, E, h, f, split
     torch.cuda.synchronize()
     ib = torch.int16 if odt == torch.bfloat16 else torch.int32
     assert torch.equal(y_one.view(ib), y_two.view(ib))
-    assert (written is None) == split[dtype]
-    if split[dtype]:
+    assert (written is None) == sums[dtype]
+    if sums[dtype]:
         assert bool((scratch == 5.0).all())
     offsets = d.offsets.cpu().numpy()
     row_src = d.row_src.cpu().numpy()[:offsets[-1]]
@@ -621,7 +621,7 @@ def test_gather_combine_matches_two_calls(dtype, out_dtype, T, k, E, h, f, split
 @pytest.mark.parametrize("dtype,out_dtype", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32")])
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
 @pytest.mark.parametrize("T,E,h,f", [(700, 6, 256, 200), (90, 3, 72, 128), (1300, 5, 768, 384),
-                                     (100, 3, 128, 1024)])  # split down K: weighted sum in the reduce
+                                     (100, 3, 128, 1024)])  # fp32: K in parts, the weights applied where they are added
 def test_top1_step_writes_weighted_rows(dtype, out_dtype, act, T, E, h, f):
     """moe_expert_ffn_shard_top1 = the expert step plus the top-1 combine: y[t] = w[t] *
     FFN_e(x[t]).  Tokens whose only pick is invalid are dropped and left unwritten."""
@@ -834,7 +834,7 @@ def test_layer_is_deterministic():
 
 def test_layer_call_smaller_than_its_capacity():
     """A layer sized for 600 tokens, called with 256 (512 assignments, so the second product
-    splits its K): the workspace sized for the larger bound holds the split's partials."""
+    hands over fp32 sums): the workspace sized for the larger bound holds them."""
     L = synth.make("c5dec", seed=0, T=256)
     cfg = L.cfg
     dt = torch.bfloat16
@@ -850,7 +850,7 @@ def test_layer_call_smaller_than_its_capacity():
 
 
 def test_layer_is_deterministic_with_split_k():
-    """Decode-sized layer (split second product): two calls give the same bits."""
+    """Decode-sized layer (the sums handed over in fp32): two calls give the same bits."""
     L = synth.make("c5dec", seed=1)
     layer, x, bias, y1 = _gpu_layer(L)
     y1 = y1.clone()

@@ -45,9 +45,9 @@ def _noalloc(x, offsets, packed, out):
 
 
 @pytest.mark.parametrize("dtype,act,h,f,first,second", [
-    # 3000 rows (one part per K), then 200 (K of the second product in 8 parts)
+    # 3000 rows (tiles), then 200 (streamed weights)
     ("bf16", "gelu", 1024, 4096, [1400, 0, 1500, 3, 97], [120, 0, 70, 9, 1]),
-    # SwiGLU; 700 rows, then 300 (K in 4 parts)
+    # SwiGLU; 700 rows (tiles), then 300 (streamed)
     ("bf16", "swiglu", 512, 1792, [300, 200, 0, 200], [100, 0, 180, 20]),
     ("f32", "gelu", 256, 512, [250, 150, 7], [31, 0, 2]),
 ])
