@@ -132,6 +132,27 @@ TILE_FORMS = [
     ([128] * 119 + [129], 264, 136, "swiglu", "128x256 / 128x384"),
 ]
 
+# 256 x 256 tiles: (rows per expert, h, f, {act: tiles, up / down}, {act: the same beside so many
+# empty experts that there are fewer than 192 rows per expert})
+WIDE_FORMS = [
+    ([33000], 72, 1536,                     # down-projection, N below one tile
+     {"gelu": "128x256 / turns", "swiglu": "128x256 / turns"}, {"gelu": "128x256 / 128x256", "swiglu": "128x256 / 128x256"}),
+    ([16200, 31, 800, 1], 264, 1600,        # N just over a tile; last row tiles of 72, 31, 32 and 1 rows
+     {"gelu": "128x256 / turns", "swiglu": "128x256 / turns"}, {"gelu": "128x256 / 128x384", "swiglu": "128x256 / 128x384"}),
+    ([256, 8192], 776, 1700,                # whole row tiles, N = 3 tiles and 8 columns
+     {"gelu": "128x256 / turns", "swiglu": "128x256 / turns"}, {"gelu": "128x256 / 128x256", "swiglu": "128x256 / 128x256"}),
+    ([1023], 3072, 12200,                   # up-projection (K = 3072: 0.84 rounds of tiles, SwiGLU 1.7)
+     {"gelu": "turns / 128x128", "swiglu": "turns / 128x128"}, {"gelu": "pairs / 128x128", "swiglu": "pairs / 128x128"}),
+    ([1500, 700], 1536, 16900,              # ... K = 1536, 5 rounds for SwiGLU
+     {"gelu": "pairs / 128x128", "swiglu": "turns / 128x128"}, {"gelu": "pairs / 128x128", "swiglu": "pairs / 128x128"}),
+]
+
+
+def empty_beside(A, E):
+    """Empty experts that bring A rows of E experts below 192 rows per expert."""
+    return A // 192 + 1 - E
+
+
 # the same for streamed weights: weight rows x blocks of 16 rows of a workgroup; "sums": the second
 # product's fp32 sums go to the combine, in so many parts
 STREAM_FORMS = [

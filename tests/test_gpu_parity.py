@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 import synth
-from _shapes import ROUTE_FORMS, STREAM_FORMS, SUMS_FORMS, TILE_FORMS
+from _shapes import ROUTE_FORMS, STREAM_FORMS, SUMS_FORMS, TILE_FORMS, WIDE_FORMS, empty_beside
 from _util import by_expert, compare_routing, normwise, rowwise, to_dev
 
 torch = pytest.importorskip("torch")
@@ -451,19 +451,13 @@ def test_tile_shapes_agree(counts, h, f, act, form):
 
 
 @pytest.mark.parametrize("act", ["gelu", "gelu_tanh", "swiglu"])
-@pytest.mark.parametrize("counts,h,f", [
-    ([600], 72, 1536),                # down-projection on 256 x 256 tiles: N below one tile
-    ([513, 31, 800, 1], 264, 1600),   # N just over a tile; last row tiles of 1, 31 and 32 rows
-    ([256, 768], 776, 1700),          # whole row tiles, N = 3 tiles and 8 columns
-    ([1023], 3072, 12200),            # up-projection too (K = 3072: 0.84 rounds of tiles, SwiGLU 1.7)
-    ([1500, 700], 1536, 16900),       # ... K = 1536, 5 rounds for SwiGLU
-])
+@pytest.mark.parametrize("counts,h,f", [c[:3] for c in WIDE_FORMS])
 def test_wide_tiles_match_128_row_tiles(act, counts, h, f):
     """256 x 256 tiles sum every output in the same order as the 128-row tiles: the call with
     rows enough per expert for them equals, bit for bit, the same rows in a call with so many
     empty experts beside them that it takes the 128-row tiles.  fp32, bf16 and top-1 outputs."""
     A, E, dev = sum(counts), len(counts), "cuda"
-    pad = A // 192 + 1 - E  # empty experts that bring the rows per expert below 192
+    pad = empty_beside(A, E)
     assert A >= 192 * E and pad > 0
     g = torch.Generator(device=dev).manual_seed(A + h + f)
     n = lambda *shape: torch.randn(shape, generator=g, device=dev).mul_(0.05).bfloat16()  # noqa: E731

@@ -2,7 +2,7 @@
 no sizes ask for a form that is not compiled."""
 import itertools
 
-from _shapes import CUS, ROUTE_FORMS, STREAM_FORMS, SUMS_FORMS, TILE_FORMS, ask
+from _shapes import CUS, ROUTE_FORMS, STREAM_FORMS, SUMS_FORMS, TILE_FORMS, WIDE_FORMS, ask, empty_beside
 
 
 def _route(dtype, T, h, E, k, want=1):
@@ -45,6 +45,10 @@ def _ffn(A, E, h, f, act, dtype="bf16"):
 def test_expert_step_cases_reach_their_forms():
     cases = [(sum(c), len(c), h, f, act, form) for c, h, f, act, form in TILE_FORMS + STREAM_FORMS]
     cases += [(A, E, h, f, act, form) for E, A, h, f, act, form in SUMS_FORMS]
+    for c, h, f, forms, beside in WIDE_FORMS:
+        A, E = sum(c), len(c)
+        cases += [(A, E, h, f, act, form) for act, form in forms.items()]
+        cases += [(A, E + empty_beside(A, E), h, f, act, form) for act, form in beside.items()]
     got = ask([_ffn(*c[:5]) for c in cases])
     assert got == [c[5] for c in cases]
 
