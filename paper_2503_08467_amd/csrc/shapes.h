@@ -187,6 +187,13 @@ enum GemmShape {
     kTile128x384,
 };
 
+// Tiles of 256 rows that A rows of E experts take in all but unlikely routings: the experts' last
+// tiles are half full on average, two standard deviations more at most; with even routing all alike.
+inline int64_t most_tiles_256(int64_t A, int E) {
+    const double most = static_cast<double>(A - 1) / 256 + 0.5 * E + std::min(0.5 * E, std::sqrt(E / 3.0));
+    return std::max(static_cast<int64_t>(most), E * tiles_of(A, 256 * static_cast<int64_t>(E)));
+}
+
 // Expected rounds of 256 x 256 tiles over the CUs: half an empty row tile per expert.
 inline double turns_rounds(int64_t A, int E, int64_t n_tiles, int cus) {
     return (static_cast<double>(A) / 256 + 0.5 * E) * static_cast<double>(n_tiles) / cus;
@@ -199,16 +206,20 @@ inline double turns_rounds(int64_t A, int E, int64_t n_tiles, int cus) {
 //   a short K loop does not pay for its fill and the single workgroup's exposed epilogue; and where
 //   the 128 x 256 tiles have a CU each they win (16 experts, 1024 x 4096, 6144 rows 158 / 168 the
 //   step, but 8192 rows 204 / 189; 8 experts, 4096 x 3584, 1536 rows 210 / 222, but 4 experts, 2048
-//   rows 237 / 210);
-// up-projection: K = 4096 941 / 799, 369 / 307, 262 / 219 and, in less than one round of tiles,
-//   141 / 124, but 137 / 173 where the tiles are just over one round of the CUs; K = 2048
-//   419 / 378 over many rounds, a tie below; K = 1024 702 / 708.
+//   rows 237 / 210), as they do where they fit one round of two a CU and the 256 x 256 tiles may not
+//   fit theirs (8 experts, 3072 x 2816, 4674 rows the step 198 / 288, skewed 199 / 228; 32 experts, 768
+//   x 3072, 18538 rows 240 / 282; where those just fit, 64 experts, 768 x 3584, 259 / 240);
+// up-projection: K = 4096 941 / 799, 369 / 307, 262 / 219 and, where they surely fit one round of the
+//   CUs, 141 / 124; just over one round 137 / 173 (3 experts, 6144 x 2816 SwiGLU, 2429 rows the step 284 /
+//   405, 16 experts, 4096 x 1408, 3847 rows, skewed, 220 / 302, even routing 221 / 214); K = 2048 419 / 378
+//   over many rounds, a tie below; K = 1024 702 / 708.
 inline bool turns_rows(int64_t A, int E) { return A >= 192 * static_cast<int64_t>(E); }
 inline bool turns_down(int64_t A, int E, int K) { return K >= 1536 && turns_rows(A, E); }
 inline bool turns_up(int64_t A, int E, int K, int64_t n_tiles, int cus) {
     if (K % 32 != 0 || K < 1536 || !turns_rows(A, E)) return false;
     const double rounds = turns_rounds(A, E, n_tiles, cus);
-    return rounds >= 4 || (K >= 3072 && (rounds >= 1.6 || (rounds <= 1 && rounds >= 0.75)));
+    if (rounds >= 4 || K < 3072) return rounds >= 4;
+    return rounds >= 1.6 || (rounds >= 0.75 && most_tiles_256(A, E) * n_tiles <= cus);
 }
 
 // Tile shape otherwise: 128 activation rows x 256 weight rows, 32-wide K steps, three stages (two in
@@ -271,7 +282,9 @@ inline GemmShape down_shape(int64_t A, int E, int K, int N, int cus) {
     const bool fits_384 = row_tiles * n384 <= cus && (n384 * 384 <= n256 * 256 || (K < 1536 && row_tiles * n256 > cus));
     // 32 experts (1568 x 640), 9542 rows: the layer 101 us at 384 columns, 105 in turns; from
     // 375 rows per expert turns win there too (48.6 -> 45.2)
-    if (turns_down(A, E, K) && expected_tiles(A, E, n256) > cus && !(fits_384 && A < 320 * static_cast<int64_t>(E)))
+    const double tiles = expected_tiles(A, E, n256);
+    if (turns_down(A, E, K) && tiles > cus && !(tiles <= 2.0 * cus && most_tiles_256(A, E) * n256 > cus) &&
+        !(fits_384 && A < 320 * static_cast<int64_t>(E)))
         return kTurns256x256;
     return fits_384 ? kTile128x384 : kTile128x256;
 }

@@ -69,3 +69,16 @@ def test_few_tiles_take_small_ones():
     got = ask([_ffn(768, 1, 1024, 4096, "gelu"), _ffn(1536, 8, 1024, 4096, "gelu"), _ffn(6144, 16, 1024, 4096, "gelu"),
                _ffn(8192, 16, 1024, 4096, "gelu"), _ffn(3008, 64, 1024, 1024, "gelu"), _ffn(3008, 64, 768, 768, "gelu")])
     assert [a.split(" / ")[1] for a in got] == ["128x128", "128x128", "128x256", "turns", "128x256", "64x256"]
+
+
+def test_wide_tiles_that_may_not_fit_one_round():
+    # up-projection: tiles that fit one round of the CUs in any likely routing, and that may not
+    up = ask([_ffn(A, E, h, f, "swiglu") for A, E, h, f in
+              [(2048, 2, 4096, 3584), (4096, 2, 4096, 1792), (3072, 8, 4096, 1792),
+               (4096, 4, 4096, 1792), (2429, 3, 6144, 2816), (3847, 16, 4096, 1408)]])
+    assert [a.split(" / ")[0] for a in up] == ["turns"] * 3 + ["pairs"] * 3
+    # down-projection: 128-row tiles that fit one round of two a CU where 256-row ones may not fit theirs
+    down = ask([_ffn(A, E, h, f, "gelu") for A, E, h, f in
+                [(4674, 8, 3072, 2816), (5170, 2, 3072, 3072), (3674, 12, 3072, 3072), (18538, 32, 768, 3072),
+                 (16384, 4, 1024, 4096), (8192, 16, 1024, 4096)]])
+    assert [a.split(" / ")[1] for a in down] == ["128x256"] * 4 + ["turns"] * 2
